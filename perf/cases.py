@@ -109,29 +109,29 @@ def _step_counts(case):
 
 
 def _fill(bufs, grads, case, seed):
-    """Fills the given [n, ld] buffers (None: not wanted) from the seed, row by row."""
+    """Fills columns [0, P) of the given buffers (None: not wanted) from the seed, row by row."""
     x = bufs["x"]
-    n, ld, dev = x.shape[0], x.shape[1], x.device
+    n, P, dev = x.shape[0], case["P"], x.device
     gen = torch.Generator(device=dev)
     gen.manual_seed(seed)
 
     def normal(std):
-        return torch.empty(ld, dtype=torch.float32, device=dev).normal_(0.0, std, generator=gen)
+        return torch.empty(P, dtype=torch.float32, device=dev).normal_(0.0, std, generator=gen)
 
     start = normal(0.02)
     for i in range(n):
         xi = start + normal(0.002)
-        x[i].copy_(xi)
+        x[i, :P].copy_(xi)
         if bufs.get("y") is not None:
-            bufs["y"][i].copy_(xi + normal(0.01))
-        bufs["m"][i].copy_(normal(0.3))
-        bufs["v"][i].uniform_(0.6, 1.4, generator=gen)
+            bufs["y"][i, :P].copy_(xi + normal(0.01))
+        bufs["m"][i, :P].copy_(normal(0.3))
+        bufs["v"][i, :P].copy_(torch.empty(P, dtype=torch.float32, device=dev).uniform_(0.6, 1.4, generator=gen))
         if bufs.get("u") is not None:
-            bufs["u"][i].copy_(normal(0.01))
+            bufs["u"][i, :P].copy_(normal(0.01))
         if bufs.get("zp") is not None:
-            bufs["zp"][i].copy_(xi + normal(0.005))
+            bufs["zp"][i, :P].copy_(xi + normal(0.005))
         if grads is not None:
-            grads[i].copy_(normal(1.0) + 0.1 * (i % 3 - 1))
+            grads[i, :P].copy_(normal(1.0) + 0.1 * (i % 3 - 1))
 
 
 def prepare(case, seed):
@@ -304,12 +304,11 @@ def _exact_steps(c, y, m, v, grads, moving):
 
 def exact(case, seed):
     n, P, dev = case["n"], case["P"], "cuda"
-    ld = (P + 7) // 8 * 8 if case["dtype"] == "bf16" else (P + 3) // 4 * 4
     pdt = torch.bfloat16 if case["dtype"] == "bf16" else torch.float32
     form, kind = case["form"], case["pass"]
 
     def buf(dtype=torch.float32, wanted=True):
-        return torch.empty((n, ld), dtype=dtype, device=dev) if wanted else None
+        return torch.empty((n, P), dtype=dtype, device=dev) if wanted else None
 
     with_u = form != "dadam"
     bufs = {"x": buf(pdt), "y": buf(pdt), "m": buf(), "v": buf(), "u": buf(wanted=with_u),

@@ -49,15 +49,16 @@ CSRC = os.path.join(ROOT, "paper_2606_11081_amd", "csrc")
 # counter summary stays valid while its family's sources are unchanged
 KERNEL_FAMILIES = {
     "adamw": ("device_common.h", "internal.h", "adamw.hip", "runtime.cpp"),
-    "phase": ("device_common.h", "internal.h", "round_phase.hip", "reductions.hip", "runtime.cpp"),
-    "planned": ("device_common.h", "internal.h", "round_planned.hip", "reductions.hip", "runtime.cpp", "plan.cpp"),
+    "phase": ("device_common.h", "internal.h", "round_tile.hip", "round_phase.hip", "reductions.hip", "runtime.cpp"),
+    "planned": ("device_common.h", "internal.h", "round_tile.hip", "round_planned.hip", "reductions.hip", "runtime.cpp",
+                "plan.cpp"),
 }
 
 
 def kernel_family(kernel, n):
     """Family of the kernel behind a profiled role: AdamW, or the gossip
-    kernel the library picks for n workers (the planned kernel beyond 16,
-    unless GASLOC_GOSSIP_KERNEL forces one)."""
+    kernels that may run the round (the tile kernel, in both families, unless
+    GASLOC_GOSSIP_KERNEL forces another)."""
     if kernel == "k_local_adamw":
         return "adamw"
     forced = os.environ.get("GASLOC_GOSSIP_KERNEL", "")

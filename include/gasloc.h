@@ -27,10 +27,9 @@
  *   - A context is not thread-safe; distinct contexts are independent.
  *   - After a device error every call on the context returns GASLOC_ESTATE.
  *   - The library reads one environment variable, a test hook:
- *     GASLOC_GOSSIP_KERNEL=phase|planned forces the round kernel (by default
- *     the kernel that keeps every worker's value in LDS runs for n <= 16, the
- *     host-planned slot-reusing kernel beyond); results are bit-identical
- *     either way.
+ *     GASLOC_GOSSIP_KERNEL=phase|planned runs the rounds with one of two
+ *     independent implementations in place of the tile kernel that runs them
+ *     by default; stored results are bit-identical either way.
  */
 #ifndef GASLOC_H
 #define GASLOC_H
@@ -60,15 +59,11 @@ typedef enum {
  * Every neighbourhood contains the worker itself (section 3.1, Notation);
  * neighbourhoods are sets, and unless stated the weights are 1/|N_i|
  * (Algorithm 1's average over N_i).  Columns are ascending within a row.
- * Cost: every graph gives the same results at any n, but beyond 16 workers
- * the round keeps each column's live values in LDS, so graphs whose distinct
- * rows need many of them at once run well below the HBM rate: the static
- * exponential graph (28 to 54 live) at n = 32-64 ran at 31-54% of peak
- * bandwidth, the sparse 1-Peer, 2-Peer, ring and random 3-regular graphs at
- * 63-77% (the low end where the buffers' physical placement is unfavourable:
- * the same round on other allocations runs at the high end).  Rows that are all the same (the complete graph, DiLoCo) share one
- * running sum instead: 63-77% of peak in fp32, 40-75% in bf16.  Use the
- * exponential graph beyond 16 workers for checks, not for speed. */
+ * Cost: the round keeps one value of every worker in LDS per column, so the
+ * graph matters little: the fused step and round ran at 62-77% of peak HBM
+ * bandwidth on every graph at n = 2 to 64 (the spread is mostly where the
+ * buffers lie in physical memory).  Rows that are all the same (the complete
+ * graph, DiLoCo) share one sum per column. */
 typedef enum {
   GASLOC_TOPO_EXPLICIT = 0,       /* the caller passes W to every round            */
   GASLOC_TOPO_RING = 1,           /* static cycle {i-1, i, i+1} (Tables 1-3 "ring")  */

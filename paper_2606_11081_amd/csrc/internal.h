@@ -1,6 +1,7 @@
 // Internal interfaces between the C ABI (runtime.cpp), the schedule
 // generator (topology.cpp), the visit planner (plan.cpp) and the HIP kernels
-// (adamw.hip, round_phase.hip, round_planned.hip, reductions.hip, with the
+// (adamw.hip, round_tile.hip, round_phase.hip, round_planned.hip,
+// reductions.hip, with the
 // device helpers of device_common.h).  Not installed.
 #pragma once
 
@@ -96,10 +97,11 @@ struct GossipArgs {
   const int32_t* ops;
   int32_t slots;
 
-  // rows that all hold the same entries (k_gossip_shared only): bit j of
-  // shared_mask says column j is an entry, with weight shared_w[j]
-  uint64_t shared_mask;
-  float shared_w[kMaxReplicas];
+  // k_gossip_tile only: byte offsets in LDS of the stored rows (0: they take
+  // the slots' place) and of the shared neighbour sums; whether every row
+  // holds the entries of row 0
+  int32_t kept_off, sums_off;
+  int32_t rows_equal;
 
   // Fused last local step (the fused kernel only): every worker i with bit i
   // of `active` first takes one AdamW step from its live iterate; the new
@@ -119,7 +121,7 @@ struct LaunchShape {
   int vec;      // columns per thread per step (1, 2 or 4)
   int threads;  // workgroup size
   int blocks;   // workgroups: one per tile of `per` steps of the workgroup
-  int batch;    // workers whose loads are issued together (1, 2, 4 or 8)
+  int batch;    // workers whose loads are issued together (1, 2, 4 or 8); tile kernel: workers per wave
   int per;      // steps (threads * vec columns each) per workgroup
 };
 
@@ -129,11 +131,13 @@ hipError_t launch_gossip_round(const GossipArgs& a, int dtype, bool fused, int f
                                const LaunchShape& shape, hipStream_t stream);
 hipError_t launch_gossip_planned(const GossipArgs& a, int dtype, bool fused, int form, const LaunchShape& shape,
                                  hipStream_t stream);
-// Rounds whose rows all hold the same entries, EQ form (round_shared.hip):
-// shape.vec must be shared_vec(n, dtype); no dynamic LDS.
-int shared_vec(int n, int dtype);
-hipError_t launch_gossip_shared(const GossipArgs& a, int dtype, bool fused, const LaunchShape& shape,
-                                hipStream_t stream);
+// Rounds with the workers spread over the waves of a workgroup
+// (round_tile.hip): shape.threads / 64 waves with shape.batch workers each (1,
+// 2, 4 or 8), kTileVec columns per lane, a.tile_groups tiles per workgroup;
+// `lds`: the bytes a.kept_off and a.sums_off were laid out in.
+constexpr int kTileVec = 4;
+hipError_t launch_gossip_tile(const GossipArgs& a, int dtype, bool fused, int form, const LaunchShape& shape,
+                              size_t lds, hipStream_t stream);
 // Workgroups of the selected phase or planned round kernel that one CU
 // holds at once, given its registers, LDS and wave limits (0 if the query
 // fails).

@@ -101,22 +101,38 @@ __global__ __launch_bounds__(256) void k_consensus_error(const void* x, int64_t 
   if (threadIdx.x == 0) partials[blockIdx.x] = total;
 }
 
+// The finalize kernels run one workgroup of kFinalizeThreads threads over at
+// most kFinalizeSegment partials: each thread's few strided loads are issued
+// together, so the kernel is one memory latency long (4096 partials: 5.9 us
+// with 256 threads of 16 loads each in turn).
+constexpr int kFinalizeThreads = 1024;
+constexpr int kFinalizeLoads = kFinalizeSegment / kFinalizeThreads;
+
+// Sum of thread's partials k, k + kFinalizeThreads, ... of a[0..count), count <= kFinalizeSegment.
+__device__ __forceinline__ double strided_sum(const double* a, int count) {
+  double v[kFinalizeLoads];
+#pragma unroll
+  for (int j = 0; j < kFinalizeLoads; ++j) {
+    const int k = threadIdx.x + j * kFinalizeThreads;
+    v[j] = k < count ? a[k] : 0.0;
+  }
+  double s = 0.0;
+#pragma unroll
+  for (int j = 0; j < kFinalizeLoads; ++j) s += v[j];
+  return s;
+}
+
 // Fixed-order sum of `count` partials into *out (one workgroup).
-__global__ __launch_bounds__(256) void k_finalize(const double* partials, int count, double* out) {
-  double v = 0.0;
-  for (int k = threadIdx.x; k < count; k += blockDim.x) v += partials[k];
-  const double total = block_sum(v);
+__global__ __launch_bounds__(kFinalizeThreads) void k_finalize(const double* partials, int count, double* out) {
+  const double total = block_sum(strided_sum(partials, count));
   if (threadIdx.x == 0) *out = total;
 }
 
 // The same for the two partial arrays of a round (consensus error, squared
 // pseudo-gradients) in one launch: out[0], out[1], each in k_finalize's order.
-__global__ __launch_bounds__(256) void k_finalize2(const double* a, const double* b, int count, double* out) {
-  double va = 0.0, vb = 0.0;
-  for (int k = threadIdx.x; k < count; k += blockDim.x) {
-    va += a[k];
-    vb += b[k];
-  }
+__global__ __launch_bounds__(kFinalizeThreads) void k_finalize2(const double* a, const double* b, int count,
+                                                                double* out) {
+  const double va = strided_sum(a, count), vb = strided_sum(b, count);
   double ta, tb;
   block_sum2(va, vb, ta, tb);
   if (threadIdx.x == 0) {
@@ -129,15 +145,12 @@ __global__ __launch_bounds__(256) void k_finalize2(const double* a, const double
 // [s * kFinalizeSegment, (s + 1) * kFinalizeSegment) of `a` (and of `b`
 // unless it is NULL; fewer in the last segment) in k_finalize's order, into
 // seg[s] (and seg[S + s]).
-__global__ __launch_bounds__(256) void k_finalize_segments(const double* a, const double* b, int count,
-                                                           double* seg) {
+__global__ __launch_bounds__(kFinalizeThreads) void k_finalize_segments(const double* a, const double* b, int count,
+                                                                        double* seg) {
   const int begin = blockIdx.x * kFinalizeSegment;
-  const int end = count - begin < kFinalizeSegment ? count : begin + kFinalizeSegment;
-  double va = 0.0, vb = 0.0;
-  for (int k = begin + threadIdx.x; k < end; k += blockDim.x) {
-    va += a[k];
-    if (b) vb += b[k];
-  }
+  const int here = count - begin < kFinalizeSegment ? count - begin : kFinalizeSegment;
+  const double va = strided_sum(a + begin, here);
+  const double vb = b ? strided_sum(b + begin, here) : 0.0;
   double ta, tb;
   block_sum2(va, vb, ta, tb);
   if (threadIdx.x == 0) {
@@ -209,19 +222,19 @@ hipError_t launch_consensus_error(const void* x, int dtype, int64_t ld, int n, i
 hipError_t launch_finalize_large(const double* a, int count, double* seg, double* out, hipStream_t stream) {
   if (count <= kFinalizeSegment) return launch_finalize(a, count, out, stream);
   const int segments = (count + kFinalizeSegment - 1) / kFinalizeSegment;
-  hipLaunchKernelGGL(k_finalize_segments, dim3(segments), dim3(256), 0, stream, a, nullptr, count, seg);
+  hipLaunchKernelGGL(k_finalize_segments, dim3(segments), dim3(kFinalizeThreads), 0, stream, a, nullptr, count, seg);
   const hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   return launch_finalize(seg, segments, out, stream);
 }
 
 hipError_t launch_finalize(const double* partials, int count, double* out, hipStream_t stream) {
-  hipLaunchKernelGGL(k_finalize, dim3(1), dim3(256), 0, stream, partials, count, out);
+  hipLaunchKernelGGL(k_finalize, dim3(1), dim3(kFinalizeThreads), 0, stream, partials, count, out);
   return hipGetLastError();
 }
 
 hipError_t launch_finalize2(const double* a, const double* b, int count, double* out, hipStream_t stream) {
-  hipLaunchKernelGGL(k_finalize2, dim3(1), dim3(256), 0, stream, a, b, count, out);
+  hipLaunchKernelGGL(k_finalize2, dim3(1), dim3(kFinalizeThreads), 0, stream, a, b, count, out);
   return hipGetLastError();
 }
 
@@ -229,7 +242,7 @@ hipError_t launch_finalize2_large(const double* a, const double* b, int count, d
                                   hipStream_t stream) {
   if (count <= kFinalizeSegment) return launch_finalize2(a, b, count, out, stream);
   const int segments = (count + kFinalizeSegment - 1) / kFinalizeSegment;
-  hipLaunchKernelGGL(k_finalize_segments, dim3(segments), dim3(256), 0, stream, a, b, count, seg);
+  hipLaunchKernelGGL(k_finalize_segments, dim3(segments), dim3(kFinalizeThreads), 0, stream, a, b, count, seg);
   const hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   return launch_finalize2(seg, seg + segments, segments, out, stream);

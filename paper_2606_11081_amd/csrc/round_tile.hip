@@ -1,0 +1,347 @@
+// a2-a5 with the workers of a column spread over the waves of a workgroup.  A
+// workgroup takes a tile of C = 64 V columns of every worker: wave w owns the
+// workers w, w + W, w + 2W, ... (K of them at most, W waves), each lane V
+// consecutive columns of each.  The thread that loads a worker's streams also
+// finishes that worker's row, so every stream is read once, in one go, before
+// the first barrier, and what the row needs again (its own term, x, u) stays
+// in registers; only the mixed values (z for EQ, the live local iterate for
+// ALG1, x for the DAdam forms) cross waves, through LDS.  The stored rows go
+// through LDS too, so that one thread per column sums the consensus error of
+// all workers in worker order.  Per element the arithmetic is exactly that of
+// k_gossip_round<..., FORM>.
+//
+// What bounds it: HBM.  Where a thread owns all workers of its columns, LDS (4
+// n bytes a column) bounds the columns in flight and a wave walks n workers in
+// turn, twice (values, then rows); here the same LDS serves n times as many
+// lanes, all loads of a tile are in flight at once, and the time between a
+// workgroup's barriers is covered by the other workgroups of the CU.  Measured
+// on MI355X against those kernels (phase up to 16 workers, planned beyond),
+// same buffers, fused step + round unless noted: n=16, P=50M bf16 Algorithm 1
+// 2-Peer 6.08 -> 4.96 ms (5.2 TB/s); n=32, P=25M bf16 complete 8.17 -> 6.41;
+// n=32, P=12M exponential (step, then round) 4.37 -> 3.80; n=64, P=6M
+// exponential 6.86 -> 2.84 (5.9 TB/s); n=32, P=40M bf16 3-regular 9.22 -> 8.78;
+// n=8, P=124M exponential 8.59 -> 7.92; n=16, P=100M (H=2) 22.43 -> 22.03; n=64,
+// P=25M matching (half the workers, gamma = 0) 9.70 -> 9.49; n=4, P=67M fp32
+// 2.45 -> 2.46.  4 columns per lane: 2 (half the bytes per access) took 3 to
+// 40% longer; tiles of 512 or 1024 columns 1 to 5% longer (n=8, n=16), as did
+// giving each XCD 4 or 16 consecutive tiles.
+#pragma clang fp contract(off)
+
+#include "device_common.h"
+
+namespace gasloc {
+namespace {
+
+typedef const __attribute__((address_space(4))) int32_t uniform_i32;
+typedef const __attribute__((address_space(4))) float uniform_f32;
+
+// What a worker's row needs after the barrier, by form: EQ the consensus
+// momentum term; ALG1 x and u; DAdam y - x; Local-DAdam x, y and u.
+template <int V, int FORM>
+struct RowKept {
+  static constexpr int count = FORM == GASLOC_FORM_ALG1 ? 2 : (FORM == GASLOC_FORM_LOCAL_DADAM ? 3 : 1);
+  float v[count][V];
+};
+
+// The streams of one worker as loaded.
+template <int V, bool FUSED, int FORM>
+struct WorkerLoads {
+  float x[V], y[V], u[V], zp[V];
+  float g[FUSED ? V : 1], m[FUSED ? V : 1], v[FUSED ? V : 1];
+};
+
+template <int DT, int V, bool FUSED, int FORM>
+__device__ __forceinline__ void tile_load(const GossipArgs& a, int i, int64_t tile0, int at, int cnt,
+                                          WorkerLoads<V, FUSED, FORM>& w) {
+  constexpr bool kEq = FORM == GASLOC_FORM_EQ;
+  constexpr int sp = DT == GASLOC_BF16 ? 2 : 4;
+  const int64_t row = static_cast<int64_t>(i) * a.ld + tile0;  // uniform
+  load_params<DT, V>(static_cast<const char*>(a.x) + row * sp, at, cnt, w.x);
+  if ((a.stepped >> i) & 1ull) {
+    load_params<DT, V>(static_cast<const char*>(a.y) + row * sp, at, cnt, w.y);
+  } else {
+#pragma unroll
+    for (int c = 0; c < V; ++c) w.y[c] = w.x[c];
+  }
+  if constexpr (FUSED) {
+    if ((a.active >> i) & 1ull) {
+      load_f32<V>(a.g + static_cast<int64_t>(i) * a.gld + tile0 + at, cnt, w.g);
+      load_f32<V>(a.m + row + at, cnt, w.m);
+      load_f32<V>(a.v + row + at, cnt, w.v);
+    }
+  }
+  if (FORM != GASLOC_FORM_DADAM && a.use_u) {
+    load_f32<V>(a.u + row + at, cnt, w.u);
+  } else {
+#pragma unroll
+    for (int c = 0; c < V; ++c) w.u[c] = 0.0f;
+  }
+  if (kEq && a.apply_gamma) load_f32<V>(a.zp + row + at, cnt, w.zp);
+}
+
+template <int DT, int V, bool FUSED, int FORM>
+__device__ __forceinline__ void tile_produce(const GossipArgs& a, int i, int64_t tile0, int at, int cnt,
+                                             WorkerLoads<V, FUSED, FORM>& w, float* slot, RowKept<V, FORM>& kept,
+                                             double& pg) {
+  const int64_t row = static_cast<int64_t>(i) * a.ld + tile0;  // uniform
+  if constexpr (FUSED) {
+    if ((a.active >> i) & 1ull) {
+      const float s1 = a.s1[i], c2 = a.c2[i];
+#pragma unroll
+      for (int c = 0; c < V; ++c)
+        w.y[c] = as_stored<DT>(adamw_element(w.y[c], w.g[c], w.m[c], w.v[c], a.c_wd, a.b1, a.omb1, a.b2, a.omb2,
+                                             a.eps, s1, c2));
+      store_f32<V>(a.m + row + at, cnt, w.m);
+      store_f32<V>(a.v + row + at, cnt, w.v);
+    }
+  }
+#pragma unroll
+  for (int c = 0; c < V; ++c) {
+    const double d = static_cast<double>(w.x[c] - w.y[c]);
+    if (c < cnt) pg += d * d;
+  }
+  float out[V];
+  if constexpr (FORM == GASLOC_FORM_EQ) {
+#pragma unroll
+    for (int c = 0; c < V; ++c) {
+      out[c] = outer_step(w.x[c], w.x[c] - w.y[c], w.u[c], a.mu, a.eta, a.nesterov);
+      kept.v[0][c] = a.gamma * (out[c] - w.zp[c]);
+    }
+    if (a.use_u) store_f32<V>(a.u + row + at, cnt, w.u);
+    if (a.store_zp) store_f32<V>(a.zp + row + at, cnt, out);
+  } else {
+#pragma unroll
+    for (int c = 0; c < V; ++c) {
+      out[c] = FORM == GASLOC_FORM_ALG1 ? w.y[c] : w.x[c];
+      if constexpr (FORM == GASLOC_FORM_ALG1) {
+        kept.v[0][c] = w.x[c];
+        kept.v[1][c] = w.u[c];
+      } else if constexpr (FORM == GASLOC_FORM_DADAM) {
+        kept.v[0][c] = w.y[c] - w.x[c];
+      } else {
+        kept.v[0][c] = w.x[c];
+        kept.v[1][c] = w.u[c];
+        kept.v[2][c] = w.y[c];
+      }
+    }
+  }
+#pragma unroll
+  for (int c = 0; c < V; ++c) slot[c] = out[c];
+}
+
+// Row i from the slots: res, and u where the form updates it there.
+template <int V, int FORM>
+__device__ __forceinline__ void tile_row(const GossipArgs& a, uniform_i32* rp, uniform_i32* col, uniform_f32* val,
+                                         int i, const float* zs, const float* shared_sum, int at,
+                                         RowKept<V, FORM>& kept, float (&res)[V]) {
+  constexpr int C = kWave * V;
+  constexpr bool kDiff = FORM == GASLOC_FORM_ALG1 || FORM == GASLOC_FORM_LOCAL_DADAM;
+#pragma unroll
+  for (int c = 0; c < V; ++c) res[c] = 0.0f;
+  if (!kDiff && shared_sum) {
+#pragma unroll
+    for (int c = 0; c < V; ++c) res[c] = shared_sum[at + c];
+  } else {
+    const int kb = rp[i], ke = rp[i + 1];
+    for (int k0 = kb; k0 < ke; k0 += 4) {
+      float zk[4][V], wk[4];
+#pragma unroll
+      for (int t = 0; t < 4; ++t) {
+        if (k0 + t >= ke) break;
+        const float* src = zs + col[k0 + t] * C + at;
+        wk[t] = val[k0 + t];
+#pragma unroll
+        for (int c = 0; c < V; ++c) zk[t][c] = src[c];
+      }
+#pragma unroll
+      for (int t = 0; t < 4; ++t) {
+        if (k0 + t >= ke) break;
+#pragma unroll
+        for (int c = 0; c < V; ++c) res[c] = res[c] + wk[t] * (kDiff ? kept.v[0][c] - zk[t][c] : zk[t][c]);
+      }
+    }
+  }
+  if constexpr (FORM == GASLOC_FORM_EQ) {
+    if (a.apply_gamma) {
+#pragma unroll
+      for (int c = 0; c < V; ++c) res[c] = res[c] + kept.v[0][c];
+    }
+  } else if constexpr (FORM == GASLOC_FORM_DADAM) {
+#pragma unroll
+    for (int c = 0; c < V; ++c) res[c] = res[c] + kept.v[0][c];
+  } else {
+#pragma unroll
+    for (int c = 0; c < V; ++c)
+      res[c] = outer_step(kept.v[FORM == GASLOC_FORM_ALG1 ? 0 : 2][c], res[c], kept.v[1][c], a.mu, a.eta, a.nesterov);
+  }
+}
+
+// What a stored value is kept as in LDS for the consensus error.
+template <int DT>
+struct KeptWord {
+  typedef float type;
+};
+template <>
+struct KeptWord<GASLOC_BF16> {
+  typedef uint16_t type;
+};
+
+// One tile.  TAIL: the tile runs past P (cnt < V in some lanes).
+template <int DT, int V, int K, bool FUSED, int FORM, bool TAIL>
+__device__ __forceinline__ void tile_round(const GossipArgs& a, unsigned char* lds, int64_t tile0, double& ce,
+                                           double& pg) {
+  typedef typename KeptWord<DT>::type kept_t;
+  constexpr int C = kWave * V;
+  constexpr int sp = DT == GASLOC_BF16 ? 2 : 4;
+  constexpr int B = K < 2 ? K : 2;  // workers whose loads are issued together (4: no faster; spills when fused)
+  const int n = a.n;
+  const int lane = threadIdx.x % kWave;
+  const int wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x) / kWave);
+  const int waves = blockDim.x / kWave;
+  const int at = lane * V;
+  int cnt = V;
+  if constexpr (TAIL) {
+    const int64_t left = a.P - tile0 - at;
+    cnt = left >= V ? V : (left > 0 ? static_cast<int>(left) : 0);
+  }
+  float* zs = reinterpret_cast<float*>(lds);
+  kept_t* xs = reinterpret_cast<kept_t*>(lds + a.kept_off);
+  float* sums = reinterpret_cast<float*>(lds + a.sums_off);
+  uniform_i32* rp = (uniform_i32*)(a.row_ptr);
+  uniform_i32* col = (uniform_i32*)(a.col);
+  uniform_f32* val = (uniform_f32*)(a.val);
+
+  RowKept<V, FORM> kept[K];
+#pragma unroll
+  for (int k0 = 0; k0 < K; k0 += B) {
+    WorkerLoads<V, FUSED, FORM> w[B];
+#pragma unroll
+    for (int b = 0; b < B; ++b) {
+      const int i = wave + (k0 + b) * waves;
+      if (i < n) tile_load<DT, V, FUSED, FORM>(a, i, tile0, at, cnt, w[b]);
+    }
+#pragma unroll
+    for (int b = 0; b < B; ++b) {
+      const int i = wave + (k0 + b) * waves;
+      if (i < n) tile_produce<DT, V, FUSED, FORM>(a, i, tile0, at, cnt, w[b], zs + i * C + at, kept[k0 + b], pg);
+    }
+  }
+  __syncthreads();  // every worker's value is in its slot
+  constexpr bool kSums = FORM == GASLOC_FORM_EQ || FORM == GASLOC_FORM_DADAM;
+  const bool shared = kSums && a.rows_equal;
+  if (shared) {
+    const int entries = rp[1];
+    for (int c = threadIdx.x; c < C; c += blockDim.x) {
+      float s = 0.0f;
+      for (int k = 0; k < entries; ++k) s = s + val[k] * zs[col[k] * C + c];
+      sums[c] = s;
+    }
+    __syncthreads();
+  }
+  float res[K][V];
+#pragma unroll
+  for (int k = 0; k < K; ++k) {
+    const int i = wave + k * waves;
+    if (i < n) tile_row<V, FORM>(a, rp, col, val, i, zs, shared ? sums : nullptr, at, kept[k], res[k]);
+  }
+  if (a.kept_off == 0) __syncthreads();  // every slot has been read: the stored rows take their place
+#pragma unroll
+  for (int k = 0; k < K; ++k) {
+    const int i = wave + k * waves;
+    if (i >= n) break;
+    const int64_t row = static_cast<int64_t>(i) * a.ld + tile0;
+    float stored[V];
+    store_params<DT, V>(static_cast<char*>(a.x) + row * sp, at, cnt, res[k], stored);
+    if constexpr (FORM == GASLOC_FORM_ALG1 || FORM == GASLOC_FORM_LOCAL_DADAM) {
+      if (a.use_u) store_f32<V>(a.u + row + at, cnt, kept[k].v[1]);
+    }
+#pragma unroll
+    for (int c = 0; c < V; ++c) {
+      if constexpr (DT == GASLOC_BF16)
+        xs[i * C + at + c] = static_cast<uint16_t>(__float_as_uint(stored[c]) >> 16);
+      else
+        xs[i * C + at + c] = stored[c];
+    }
+  }
+  __syncthreads();
+  // consensus error, one column per thread, workers in order
+  const double inv_n = 1.0 / static_cast<double>(n);
+  const int cols = TAIL ? static_cast<int>(a.P - tile0 < C ? a.P - tile0 : C) : C;
+  for (int c = threadIdx.x; c < cols; c += blockDim.x) {
+    auto value = [&](int i) {
+      if constexpr (DT == GASLOC_BF16)
+        return static_cast<double>(bf16_to_f32(xs[i * C + c]));
+      else
+        return static_cast<double>(xs[i * C + c]);
+    };
+    const double shift = value(0);
+    double s = 0.0, q = 0.0;
+    for (int i = 1; i < n; ++i) {
+      const double d = value(i) - shift;
+      s += d;
+      q += d * d;
+    }
+    ce += q - s * s * inv_n;
+  }
+}
+
+template <int DT, int V, int K, bool FUSED, int FORM>
+__global__ __launch_bounds__(1024) void k_gossip_tile(GossipArgs a) {
+  extern __shared__ __align__(16) unsigned char lds[];
+  constexpr int C = kWave * V;
+  const int64_t tiles = (a.P + C - 1) / C;
+  const int64_t t0 = static_cast<int64_t>(blockIdx.x) * a.tile_groups;
+  const int64_t t1 = tiles - t0 < a.tile_groups ? tiles : t0 + a.tile_groups;
+  double ce = 0.0, pg = 0.0;
+  for (int64_t t = t0; t < t1; ++t) {
+    if (a.kept_off == 0 && t > t0) __syncthreads();  // the stored rows of the tile before have been summed
+    const int64_t tile0 = t * C;
+    if (tile0 + C <= a.P)
+      tile_round<DT, V, K, FUSED, FORM, false>(a, lds, tile0, ce, pg);
+    else
+      tile_round<DT, V, K, FUSED, FORM, true>(a, lds, tile0, ce, pg);
+  }
+  double total_ce, total_pg;
+  block_sum2(ce, pg, total_ce, total_pg);
+  if (threadIdx.x == 0) {
+    a.partials[blockIdx.x] = total_ce;
+    a.pg_partials[blockIdx.x] = total_pg;
+  }
+}
+
+template <int DT, bool FUSED, int FORM, typename F>
+hipError_t with_tile_workers(int per_wave, F& f) {
+  switch (per_wave) {
+    case 1: return f(reinterpret_cast<const void*>(&k_gossip_tile<DT, kTileVec, 1, FUSED, FORM>));
+    case 2: return f(reinterpret_cast<const void*>(&k_gossip_tile<DT, kTileVec, 2, FUSED, FORM>));
+    case 4: return f(reinterpret_cast<const void*>(&k_gossip_tile<DT, kTileVec, 4, FUSED, FORM>));
+    default: return f(reinterpret_cast<const void*>(&k_gossip_tile<DT, kTileVec, 8, FUSED, FORM>));
+  }
+}
+
+template <int DT, typename F>
+hipError_t with_tile_form(bool fused, int form, int per_wave, F& f) {
+  switch (form) {
+    case GASLOC_FORM_ALG1:
+      return fused ? with_tile_workers<DT, true, GASLOC_FORM_ALG1>(per_wave, f)
+                   : with_tile_workers<DT, false, GASLOC_FORM_ALG1>(per_wave, f);
+    case GASLOC_FORM_DADAM:
+      return with_tile_workers<DT, false, GASLOC_FORM_DADAM>(per_wave, f);
+    case GASLOC_FORM_LOCAL_DADAM:
+      return with_tile_workers<DT, false, GASLOC_FORM_LOCAL_DADAM>(per_wave, f);
+    default:
+      return fused ? with_tile_workers<DT, true, GASLOC_FORM_EQ>(per_wave, f)
+                   : with_tile_workers<DT, false, GASLOC_FORM_EQ>(per_wave, f);
+  }
+}
+
+}  // namespace
+
+hipError_t launch_gossip_tile(const GossipArgs& a, int dtype, bool fused, int form, const LaunchShape& s, size_t lds,
+                              hipStream_t stream) {
+  auto launch = [&](const void* k) { return launch_round_args(k, a, s, lds, stream); };
+  return dtype == GASLOC_BF16 ? with_tile_form<GASLOC_BF16>(fused, form, s.batch, launch)
+                              : with_tile_form<GASLOC_F32>(fused, form, s.batch, launch);
+}
+
+}  // namespace gasloc

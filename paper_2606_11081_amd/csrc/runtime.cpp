@@ -347,19 +347,6 @@ gasloc_status upload_plan(gasloc_ctx* c, const std::vector<int32_t>& ops) {
   return GASLOC_OK;
 }
 
-// Which kernel runs a round: the phase kernel keeps every worker's slot
-// value in LDS; the planned kernel (plan.cpp) keeps only the live ones and
-// lets rows with equal entries share one neighbour sum; the shared kernel
-// serves rounds whose rows all hold the same entries (the complete graph) in
-// the EQ form, with one running sum per column and each row's own term in
-// registers.  Measured on MI355X (EQ form, gossip round alone): beyond
-// 16 workers planned is faster than phase on every graph (n=64: 1-Peer 15.0 vs
-// 28.2 ms, complete 34.5 vs 247 ms; n=32: 3-regular 1.9x, complete 28.8 vs
-// 74.8 ms) or tied (n=64 exponential); at n <= 16 the phase kernel keeps more
-// loads in flight and the two tie, except the fused round (n=16 one-peer
-// exponential: 44.8 vs 45.4 ms) and the complete graph (n=16: 29.8 vs 26.1 ms).
-enum class RoundKernel { kPhase, kPlanned, kShared };
-
 // True if every row of W holds the entries of row 0 (columns and weight bits).
 bool rows_all_equal(int n, const int32_t* rp, const int32_t* col, const float* val) {
   const int32_t len = rp[1] - rp[0];
@@ -372,27 +359,70 @@ bool rows_all_equal(int n, const int32_t* rp, const int32_t* col, const float* v
   return true;
 }
 
-// The shared kernel on the complete graph (EQ, gamma = 0.1, round alone /
-// fused last step + round, against the kernel used before it): fp32 n=16,
-// P=350M 25.3-25.7 / 44.3-44.4 ms (planned 25.9-26.0 / 44.3-44.4); n=32,
-// P=150M 23.0 / 40.8 ms (planned 28.6 / 45.7); n=64, P=50M 17.8 / 34.1 ms
-// (planned 34.8 / 56.6); bf16 n=16 20.6 / 40.9 ms (phase 35.1 / 46.3); n=32
-// 23.6 / 46.6 ms (planned 30.9 / 44.6); n=64 22.0 / 34.4 ms (planned 38.1 /
-// 55.9).  So it serves every such round except the fused bf16 one at 17-32
-// workers.
-//
-// Test hook (documented in gasloc.h): GASLOC_GOSSIP_KERNEL=phase|planned forces
-// one kernel, so that the test suite can run every case through both.
-RoundKernel pick_round_kernel(const gasloc_ctx& c, const int32_t* rp, const int32_t* col, const float* val,
-                              bool fused) {
+// Which kernel runs a round.  The tile kernel (the workers of a column over
+// the waves of a workgroup) runs every round; the phase kernel (a thread owns
+// all workers of its columns, every slot value in LDS) and the planned kernel
+// (only the live ones, in the visit order of plan.cpp) are independent
+// implementations of the same arithmetic that the test hook selects
+// (documented in gasloc.h): GASLOC_GOSSIP_KERNEL=phase|planned.
+enum class RoundKernel { kTile, kPhase, kPlanned };
+
+RoundKernel pick_round_kernel() {
   if (const char* env = std::getenv("GASLOC_GOSSIP_KERNEL")) {
     if (std::strcmp(env, "phase") == 0) return RoundKernel::kPhase;
     if (std::strcmp(env, "planned") == 0) return RoundKernel::kPlanned;
   }
-  const bool fused_bf16_17_32 = fused && c.hp.param_dtype == GASLOC_BF16 && c.n > 16 && c.n <= 32;
-  if (c.hp.round_form == GASLOC_FORM_EQ && !fused_bf16_17_32 && rows_all_equal(c.n, rp, col, val))
-    return RoundKernel::kShared;
-  return c.n > 16 ? RoundKernel::kPlanned : RoundKernel::kPhase;
+  return RoundKernel::kTile;
+}
+
+// Tile kernel's launch: its LDS layout in `a`, the LDS bytes in `lds`.
+//
+// One tile per workgroup (several only if the partials buffer requires it): 2,
+// 4 and 8 tiles took 2, 5 and 8% longer (n=4, P=67M fp32, fused; the same on
+// n=2, 3, 6).  Workers per wave: with few tiles per CU the fewest that 16
+// waves allow, for the shortest chain in a wave; with many tiles twice that,
+// so that a workgroup has 8 waves or fewer and several of them, in different
+// phases, share a CU.  Fused step + round, the fewest against twice that (and
+// four times): n=16, P=65k fp32 15.8 against 14.1 (18.0) us, P=4.2M 638
+// against 655 (759) us, P=50M bf16 Algorithm 1 5.51 against 4.96 (4.87) ms;
+// n=32, P=2.1M 668 against 692 us, P=40M bf16 3-regular 9.03 against 8.78 ms;
+// n=64, P=1.05M 694 against 717 us, P=25M matching 10.17 against 9.49 ms.
+// The line is at 64 tiles per CU, between the sizes that prefer either.
+// The stored rows get LDS of their own up to 32 workers; beyond, they take the
+// slots' place after one more barrier, so that two workgroups fit a CU (n=64,
+// P=25M matching: 11.57 ms with LDS of their own, 9.42 ms in place).
+gasloc::LaunchShape pick_tile_shape(const gasloc_ctx& c, bool rows_equal, gasloc::GossipArgs* a, size_t* lds) {
+  constexpr int64_t kCols = 64 * gasloc::kTileVec;
+  const int64_t tiles = (c.P + kCols - 1) / kCols;
+  const int fewest = c.n <= 16 ? 1 : (c.n <= 32 ? 2 : 4);
+  int per_wave = tiles < 64 * static_cast<int64_t>(c.cus) ? fewest : 2 * fewest;
+  bool in_place = c.n > 32;
+  int64_t per = 1;
+#ifdef GASLOC_TUNING
+  if (const char* env = std::getenv("GASLOC_TILE")) {
+    int k = 0, p = 0, t = 0;
+    if (std::sscanf(env, "%d,%d,%d", &k, &p, &t) == 3 && (k == 1 || k == 2 || k == 4 || k == 8) && t >= 1) {
+      per_wave = 16 * k >= c.n ? k : 4;
+      in_place = p != 0;
+      per = t;
+    }
+  }
+#endif
+  per = std::max<int64_t>(per, (tiles + gasloc::kMaxPartials - 1) / gasloc::kMaxPartials);
+  const size_t slots = static_cast<size_t>(c.n) * kCols;
+  size_t end = slots * sizeof(float);
+  a->kept_off = 0;
+  if (!in_place) {
+    a->kept_off = static_cast<int32_t>(end);
+    end += slots * param_bytes(c.hp.param_dtype);
+  }
+  a->sums_off = static_cast<int32_t>(end);
+  a->rows_equal = rows_equal;
+  if (rows_equal) end += kCols * sizeof(float);
+  *lds = end;
+  const int waves = (c.n + per_wave - 1) / per_wave;
+  return gasloc::LaunchShape{gasloc::kTileVec, 64 * waves, static_cast<int>((tiles + per - 1) / per), per_wave,
+                             static_cast<int>(per)};
 }
 
 // Steps of the standalone consensus error per workgroup: 8 (as the round
@@ -501,7 +531,7 @@ gasloc_status run_round(gasloc_ctx* c, const gasloc_csr* W, uint64_t t, const St
     val = c->skip_val.data();
   }
   DeviceGuard guard(c->device);
-  const RoundKernel kernel = pick_round_kernel(*c, rp, col, val, step != nullptr);
+  const RoundKernel kernel = pick_round_kernel();
   const bool planned = kernel == RoundKernel::kPlanned;
   int slots = 0;
   if (planned) {
@@ -514,9 +544,11 @@ gasloc_status run_round(gasloc_ctx* c, const gasloc_csr* W, uint64_t t, const St
   }
   gasloc::LaunchShape shape;
   size_t lds = 0;
-  if (kernel == RoundKernel::kShared) {
-    shape = gasloc::LaunchShape{gasloc::shared_vec(c->n, c->hp.param_dtype), 256, 0, 4, 0};
-    lds = gasloc::kStaticLds;
+  const bool tile = kernel == RoundKernel::kTile;
+  gasloc::GossipArgs a{};
+  if (tile) {
+    shape = pick_tile_shape(*c, rows_all_equal(c->n, rp, col, val), &a, &lds);
+    lds += gasloc::kStaticLds;
   } else if (planned) {
     // 4 columns per thread when the plan needs few slots (n=64 1-Peer: 10.7-
     // 12.8 ms), else 2 (1 column was 25% slower).  The workgroup size is the
@@ -552,7 +584,7 @@ gasloc_status run_round(gasloc_ctx* c, const gasloc_csr* W, uint64_t t, const St
     if (step && shape.batch == 8) shape.batch = 4;  // the fused kernel batches at most 4 workers
     lds = gasloc::gossip_lds_bytes(c->n, nnz, shape) + gasloc::kStaticLds;
   }
-  tile_grid(*c, &shape, planned && slots > 8 ? 1 : 8);
+  if (!tile) tile_grid(*c, &shape, planned && slots > 8 ? 1 : 8);
   if (lds > c->lds_per_block_max) return fail(c, GASLOC_EINVAL, "gossip shape exceeds the device's LDS per workgroup");
   if (planned) {  // slot words become byte offsets for this launch's shape
     std::string err;
@@ -560,13 +592,9 @@ gasloc_status run_round(gasloc_ctx* c, const gasloc_csr* W, uint64_t t, const St
                                   &err))
       return fail(c, GASLOC_EINVAL, err);
   }
-  // the shared kernel takes row 0's weights as arguments, not from the device CSR
-  if (kernel != RoundKernel::kShared) {
-    gasloc_status st = planned ? upload_plan(c, c->plan_ops) : upload_csr(c, rp, col, val, nnz);
-    if (st != GASLOC_OK) return st;
-  }
+  gasloc_status st = planned ? upload_plan(c, c->plan_ops) : upload_csr(c, rp, col, val, nnz);
+  if (st != GASLOC_OK) return st;
 
-  gasloc::GossipArgs a{};
   a.x = c->buf.x;
   a.y = c->buf.y;
   a.u = c->buf.u;
@@ -577,7 +605,7 @@ gasloc_status run_round(gasloc_ctx* c, const gasloc_csr* W, uint64_t t, const St
   a.val = reinterpret_cast<const float*>(c->d_csr + rp_bytes + sizeof(int32_t) * c->n * c->n);
   a.ld = c->buf.ld;
   a.P = c->P;
-  a.tile_groups = static_cast<int64_t>(shape.per) * shape.threads;
+  a.tile_groups = tile ? shape.per : static_cast<int64_t>(shape.per) * shape.threads;
   a.n = c->n;
   a.nnz = nnz;
   a.mu = c->hp.outer_momentum;
@@ -606,12 +634,9 @@ gasloc_status run_round(gasloc_ctx* c, const gasloc_csr* W, uint64_t t, const St
   }
   a.partials = c->d_partials;
   a.pg_partials = c->d_partials + gasloc::kMaxPartials;
-  if (kernel == RoundKernel::kShared) {
-    for (int32_t k = rp[0]; k < rp[1]; ++k) {
-      a.shared_mask |= 1ull << col[k];
-      a.shared_w[col[k]] = val[k];
-    }
-    HIP_TRY(c, gasloc::launch_gossip_shared(a, c->hp.param_dtype, step != nullptr, shape, c->stream));
+  if (tile) {
+    HIP_TRY(c, gasloc::launch_gossip_tile(a, c->hp.param_dtype, step != nullptr, c->hp.round_form, shape,
+                                          lds - gasloc::kStaticLds, c->stream));
   } else if (planned) {
     a.ops = reinterpret_cast<const int32_t*>(c->d_csr);
     a.slots = slots;

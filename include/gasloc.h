@@ -192,8 +192,8 @@ gasloc_status gasloc_local_step(gasloc_ctx *ctx, const float *grads, int64_t gra
  *   delta = x - y;  u = mu u + delta;  z = x - eta (delta + mu u)  (Nesterov)
  *   x_i  = sum_k W_ik z_k  [+ gamma (z_i - zp_i) after the first round];
  *   zp_i = z_i  (if gamma != 0)
- * then the consensus error of the new x is reduced in fp64 and kept on the
- * device for gasloc_consensus_error.  W: the caller's CSR (host memory), or
+ * then the consensus error of the new x is reduced in fp64 and kept (in pinned
+ * host memory) for gasloc_consensus_error.  W: the caller's CSR (host memory), or
  * NULL to use the context's topology for round t (EINVAL if EXPLICIT).
  * Deferred reset: afterwards y is logically equal to x but is not written;
  * the next local step of a worker reads x.  A worker that took no local

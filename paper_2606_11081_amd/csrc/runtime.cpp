@@ -74,7 +74,7 @@ struct gasloc_ctx {
   std::vector<int64_t> k;         // AdamW step count per worker
   std::vector<uint8_t> stepped;   // local steps taken since the last round
   int64_t rounds_done = 0;
-  bool ce_current = false;        // d_ce holds the consensus error of the stored x
+  bool ce_current = false;        // h_stats[0] is (or will be, in stream order) the consensus error of the stored x
   bool failed = false;
 
   unsigned char* d_csr = nullptr;  // device copy of the round's CSR or visit plan
@@ -86,8 +86,11 @@ struct gasloc_ctx {
   // [kPartialWords]: consensus-error partials, pseudo-gradient partials (each
   // kMaxPartials), then the finalize's segment sums
   double* d_partials = nullptr;
-  double* d_ce = nullptr;  // [2]: consensus error, squared pseudo-gradients of the last round
-  double* h_ce = nullptr;  // [2] pinned
+  // [2]: consensus error, squared pseudo-gradients of the last round, in pinned
+  // host memory that the finalize kernel writes (d_stats: its device address);
+  // a reader waits for the stream and reads the host side
+  double* h_stats = nullptr;
+  double* d_stats = nullptr;
 
   size_t lds_per_block_max = 0;
   size_t lds_per_cu = 0;
@@ -277,10 +280,9 @@ void release(gasloc_ctx* c) {
     if (c->stage_done[i]) (void)hipEventDestroy(c->stage_done[i]);
     if (c->h_stage[i]) (void)hipHostFree(c->h_stage[i]);
   }
-  if (c->h_ce) (void)hipHostFree(c->h_ce);
+  if (c->h_stats) (void)hipHostFree(c->h_stats);
   if (c->d_csr) (void)hipFree(c->d_csr);
   if (c->d_partials) (void)hipFree(c->d_partials);
-  if (c->d_ce) (void)hipFree(c->d_ce);
   delete c;
 }
 
@@ -439,14 +441,18 @@ gasloc_status reduce_cols(gasloc_ctx* c, int64_t p0, int64_t p1) {
   HIP_TRY(c, gasloc::launch_consensus_error(c->buf.x, c->hp.param_dtype, c->buf.ld, c->n, p0, p1, per,
                                             c->d_partials, c->stream));
   HIP_TRY(c, gasloc::launch_finalize_large(c->d_partials, blocks, c->d_partials + 2 * gasloc::kMaxPartials,
-                                           c->d_ce, c->stream));
+                                           c->d_stats, c->stream));
   return GASLOC_OK;
 }
 
-gasloc_status read_ce(gasloc_ctx* c, double* out) {
-  HIP_TRY(c, hipMemcpyAsync(c->h_ce, c->d_ce, sizeof(double), hipMemcpyDeviceToHost, c->stream));
+// Statistic k (0: consensus error, 1: squared pseudo-gradients) once the
+// stream has passed the kernel that writes it.  The kernel stores it in host
+// memory itself: a device-to-host copy of 8 bytes put more packets and a wait
+// between the kernel and the caller (n=4, P=4099, fused round + both
+// statistics: 39.0 us with two copies, 23.2 us without).
+gasloc_status read_stat(gasloc_ctx* c, int k, double* out) {
   HIP_TRY(c, hipStreamSynchronize(c->stream));
-  *out = *c->h_ce;
+  *out = c->h_stats[k];
   return GASLOC_OK;
 }
 
@@ -647,7 +653,7 @@ gasloc_status run_round(gasloc_ctx* c, const gasloc_csr* W, uint64_t t, const St
                                            c->stream));
   }
   HIP_TRY(c, gasloc::launch_finalize2_large(c->d_partials, a.pg_partials, shape.blocks,
-                                             c->d_partials + 2 * gasloc::kMaxPartials, c->d_ce, c->stream));
+                                             c->d_partials + 2 * gasloc::kMaxPartials, c->d_stats, c->stream));
   if (step) {
     for (int i = 0; i < c->n; ++i)
       if ((step->active >> i) & 1ull) c->k[static_cast<size_t>(i)] += 1;
@@ -754,9 +760,12 @@ gasloc_status gasloc_init(int32_t n, int64_t P, const gasloc_topology* topology,
   if ((e = hipMalloc(&c->d_csr, stage_bytes(n))) != hipSuccess) return init_fail(e, "hipMalloc csr");
   if ((e = hipMalloc(&c->d_partials, sizeof(double) * kPartialWords)) != hipSuccess)
     return init_fail(e, "hipMalloc partials");
-  if ((e = hipMalloc(&c->d_ce, 2 * sizeof(double))) != hipSuccess) return init_fail(e, "hipMalloc ce");
-  if ((e = hipHostMalloc(&c->h_ce, 2 * sizeof(double), hipHostMallocDefault)) != hipSuccess)
-    return init_fail(e, "hipHostMalloc ce");
+  if ((e = hipHostMalloc(reinterpret_cast<void**>(&c->h_stats), 2 * sizeof(double),
+                         hipHostMallocMapped | hipHostMallocCoherent)) != hipSuccess)
+    return init_fail(e, "hipHostMalloc statistics");
+  c->h_stats[0] = c->h_stats[1] = 0.0;
+  if ((e = hipHostGetDevicePointer(reinterpret_cast<void**>(&c->d_stats), c->h_stats, 0)) != hipSuccess)
+    return init_fail(e, "hipHostGetDevicePointer");
   for (int i = 0; i < kStageSlots; ++i) {
     if ((e = hipHostMalloc(&c->h_stage[i], stage_bytes(n), hipHostMallocDefault)) != hipSuccess)
       return init_fail(e, "hipHostMalloc staging");
@@ -764,8 +773,6 @@ gasloc_status gasloc_init(int32_t n, int64_t P, const gasloc_topology* topology,
       return init_fail(e, "hipEventCreate");
   }
 
-  if ((e = hipMemsetAsync(c->d_ce, 0, 2 * sizeof(double), c->stream)) != hipSuccess)
-    return init_fail(e, "hipMemsetAsync");
   // zero the optimizer state of every worker, m, v, u, zp: columns [0, P) of
   // each row only (the row padding is the caller's)
   for (float* p : {b.m, b.v, b.u, b.zp}) {
@@ -845,17 +852,14 @@ gasloc_status gasloc_consensus_error(gasloc_ctx* c, double* out) {
     if (st != GASLOC_OK) return st;
     c->ce_current = true;
   }
-  return read_ce(c, out);
+  return read_stat(c, 0, out);
 }
 
 gasloc_status gasloc_pseudo_gradient_sq(gasloc_ctx* c, double* out) {
   if (!c || !out) return fail(c, GASLOC_EINVAL, "NULL argument");
   if (c->failed) return fail(c, GASLOC_ESTATE, "context unusable after a device error: " + c->err);
   DeviceGuard guard(c->device);
-  HIP_TRY(c, hipMemcpyAsync(c->h_ce + 1, c->d_ce + 1, sizeof(double), hipMemcpyDeviceToHost, c->stream));
-  HIP_TRY(c, hipStreamSynchronize(c->stream));
-  *out = c->h_ce[1];
-  return GASLOC_OK;
+  return read_stat(c, 1, out);
 }
 
 gasloc_status gasloc_consensus_error_cols(gasloc_ctx* c, int64_t p_begin, int64_t p_end, double* out) {
@@ -866,8 +870,8 @@ gasloc_status gasloc_consensus_error_cols(gasloc_ctx* c, int64_t p_begin, int64_
   DeviceGuard guard(c->device);
   gasloc_status st = reduce_cols(c, p_begin, p_end);
   if (st != GASLOC_OK) return st;
-  c->ce_current = false;  // d_ce now holds a partial sum
-  return read_ce(c, out);
+  c->ce_current = false;  // h_stats[0] now is a partial sum
+  return read_stat(c, 0, out);
 }
 
 gasloc_status gasloc_replica_mean(gasloc_ctx* c, void* out) {

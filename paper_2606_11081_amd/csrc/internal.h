@@ -145,10 +145,13 @@ int phase_blocks_per_cu(int dtype, bool fused, int form, const LaunchShape& shap
 int planned_blocks_per_cu(int dtype, bool fused, int form, const LaunchShape& shape, size_t dyn_lds);
 // Dynamic LDS bytes of one workgroup of the planned kernel (z slots only).
 size_t planned_lds_bytes(int slots, const LaunchShape& shape);
-// The standalone consensus error of columns [p_begin, p_end): one partial
-// per workgroup of kReduceThreads threads, each taking `per` consecutive
-// steps of 16-byte column groups; consensus_error_blocks gives the count.
-constexpr int kReduceThreads = 256;
+// The standalone consensus error of columns [p_begin, p_end): one partial per
+// workgroup of reduce_threads(dtype) threads, each taking `per` consecutive
+// steps of kReduceVec columns; consensus_error_blocks gives the count.  A step
+// of a workgroup is 1024 fp32 or 2048 bf16 columns.
+constexpr int kReduceVec = 4;
+constexpr int reduce_threads(int dtype) { return dtype == GASLOC_BF16 ? 512 : 256; }
+constexpr int reduce_step(int dtype) { return kReduceVec * reduce_threads(dtype); }
 int consensus_error_blocks(int dtype, int64_t p_begin, int64_t p_end, int per);
 hipError_t launch_consensus_error(const void* x, int dtype, int64_t ld, int n, int64_t p_begin,
                                   int64_t p_end, int per, double* partials, hipStream_t stream);
@@ -166,8 +169,8 @@ hipError_t launch_finalize2_large(const double* a, const double* b, int count, d
 // *out = the sum of a[0..count), count <= kMaxPartials, in the same
 // segmented order (seg: at least ceil(count / kFinalizeSegment) doubles).
 hipError_t launch_finalize_large(const double* a, int count, double* seg, double* out, hipStream_t stream);
-// The network average of columns [0, P), workgroups as for the consensus error.
-hipError_t launch_replica_mean(const void* x, int dtype, int64_t ld, int n, int64_t P, int per, void* out,
+// The network average of columns [0, P), one step per workgroup.
+hipError_t launch_replica_mean(const void* x, int dtype, int64_t ld, int n, int64_t P, void* out,
                                hipStream_t stream);
 
 // Dynamic LDS bytes one workgroup of the gossip kernel needs (z slots of

@@ -20,6 +20,17 @@ static __device__ __align__(256) double scratch[kNoAllocPartials + kNoAllocSegme
 namespace gasloc {
 namespace {
 
+// What bounds both reductions is HBM, once the fp64 work (a conversion and
+// one or four operations an element) does not: a group of 4 columns per thread
+// keeps its sums in few registers, and a step that lies in the range as a whole
+// tests nothing per lane, so that the loads of a batch are issued back to back.
+// n=16, P=50M bf16: the error 350 -> 254 us (6.3 TB/s), the mean 354 -> 274 us;
+// n=16, P=50M fp32: 478 (6.7 TB/s), 620 -> 592 us; n=64, P=6M bf16: 175 -> 148,
+// 145 -> 144 us.  With 8 bf16 columns per thread the error took 350 us, with
+// whole batches split from the last one (more registers) 294, with batches of
+// 8 workers the same as with 4.
+constexpr int kErrorBatch = 4;  // workers whose loads are in flight at a time
+
 // Columns [lo, hi) of the V-column group at idx (the others read as 0): a
 // vector load when the whole group is in range.
 template <int DT, int V>
@@ -41,61 +52,75 @@ __device__ __forceinline__ void load_cols(const void* base, int64_t idx, int lo,
   }
 }
 
-// A thread takes a group of columns of every worker (4 fp32 or 8 bf16, i.e.
-// 16 bytes; groups are aligned so every row's vector loads are, and the
-// groups at the ends of the range are masked), with the loads of 8 workers
-// (fp32) or 4 (bf16, twice the columns; 8 left it register-bound) in
-// flight.  Per column the sums are those of the fused kernel: shifted by
-// worker 0's value, fp64, workers in order.  Workgroup b takes the `per`
-// consecutive steps of blockDim.x groups starting at group b * per *
-// blockDim.x (tile order, as the round kernels) and writes one partial.
-template <int DT>
-__global__ __launch_bounds__(256) void k_consensus_error(const void* x, int64_t ld, int n,
-                                                         int64_t p_begin, int64_t p_end, int per,
-                                                         double* partials) {
-  constexpr int V = DT == GASLOC_BF16 ? 8 : 4, R = DT == GASLOC_BF16 ? 4 : 8;
+// One group of a thread: the shifted fp64 sums of its 4 columns of every
+// worker, workers in order, as the fused kernel's.  EDGE: the group may be cut
+// by an end of the range (columns [lo, hi) of it count).
+template <int DT, bool EDGE>
+__device__ __forceinline__ double group_error(const void* x, int64_t ld, int n, int64_t p, int lo_edge, int hi_edge) {
+  constexpr int V = kReduceVec, R = kErrorBatch;
+  const int lo = EDGE ? lo_edge : 0, hi = EDGE ? hi_edge : V;
+  double shift[V], s[V], q[V];
+  {
+    float v[V];
+    load_cols<DT, V>(x, p, lo, hi, v);
+#pragma unroll
+    for (int c = 0; c < V; ++c) {
+      shift[c] = static_cast<double>(v[c]);
+      s[c] = 0.0;
+      q[c] = 0.0;
+    }
+  }
+  for (int i0 = 1; i0 < n; i0 += R) {
+    float v[R][V];
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      if (i0 + r >= n) break;
+      load_cols<DT, V>(x, static_cast<int64_t>(i0 + r) * ld + p, lo, hi, v[r]);
+    }
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      if (i0 + r >= n) break;
+#pragma unroll
+      for (int c = 0; c < V; ++c) {
+        const double d = static_cast<double>(v[r][c]) - shift[c];
+        s[c] += d;
+        q[c] = __builtin_fma(d, d, q[c]);
+      }
+    }
+  }
   const double inv_n = 1.0 / static_cast<double>(n);
+  double ce = 0.0;
+#pragma unroll
+  for (int c = 0; c < V; ++c)
+    if (c >= lo && c < hi) ce += q[c] - s[c] * s[c] * inv_n;
+  return ce;
+}
+
+// A thread takes groups of 4 columns of every worker (groups are aligned so
+// every row's vector loads are, and those at the ends of the range are
+// masked; a step of the workgroup without such a group tests nothing per lane).
+// Workgroup b takes the `per` consecutive steps of blockDim.x groups starting
+// at group b * per * blockDim.x (tile order, as the round kernels) and writes
+// one partial.
+template <int DT>
+__global__ __launch_bounds__(reduce_threads(DT)) void k_consensus_error(const void* x, int64_t ld, int n,
+                                                                        int64_t p_begin, int64_t p_end, int per,
+                                                                        double* partials) {
+  constexpr int V = kReduceVec;
   const int64_t base = p_begin - p_begin % V;
   const int64_t groups = (p_end - base + V - 1) / V;
   const int64_t g0 = static_cast<int64_t>(blockIdx.x) * per * blockDim.x;
   const int64_t g_end = groups - g0 < static_cast<int64_t>(per) * blockDim.x ? groups : g0 + per * blockDim.x;
   double ce = 0.0;
-  for (int64_t gi = g0 + threadIdx.x; gi < g_end; gi += blockDim.x) {
-    const int64_t p = base + gi * V;
-    const int lo = p < p_begin ? static_cast<int>(p_begin - p) : 0;
-    const int hi = p_end - p < V ? static_cast<int>(p_end - p) : V;
-    double shift[V], s[V], q[V];
-    {
-      float v[V];
-      load_cols<DT, V>(x, p, lo, hi, v);
-#pragma unroll
-      for (int c = 0; c < V; ++c) {
-        shift[c] = static_cast<double>(v[c]);
-        s[c] = 0.0;
-        q[c] = 0.0;
-      }
+  for (int64_t g = g0; g < g_end; g += blockDim.x) {
+    const int64_t p = base + (g + threadIdx.x) * V;
+    if (base + g * V >= p_begin && base + (g + blockDim.x) * V <= p_end) {
+      ce += group_error<DT, false>(x, ld, n, p, 0, V);
+    } else if (p < p_end) {
+      const int lo = p < p_begin ? static_cast<int>(p_begin - p) : 0;
+      const int hi = p_end - p < V ? static_cast<int>(p_end - p) : V;
+      ce += group_error<DT, true>(x, ld, n, p, lo, hi);
     }
-    for (int i0 = 1; i0 < n; i0 += R) {
-      float v[R][V];
-#pragma unroll
-      for (int r = 0; r < R; ++r) {
-        if (i0 + r >= n) break;
-        load_cols<DT, V>(x, static_cast<int64_t>(i0 + r) * ld + p, lo, hi, v[r]);
-      }
-#pragma unroll
-      for (int r = 0; r < R; ++r) {
-        if (i0 + r >= n) break;
-#pragma unroll
-        for (int c = 0; c < V; ++c) {
-          const double d = static_cast<double>(v[r][c]) - shift[c];
-          s[c] += d;
-          q[c] += d * d;
-        }
-      }
-    }
-#pragma unroll
-    for (int c = 0; c < V; ++c)
-      if (c >= lo && c < hi) ce += q[c] - s[c] * s[c] * inv_n;
   }
   const double total = block_sum(ce);
   if (threadIdx.x == 0) partials[blockIdx.x] = total;
@@ -159,50 +184,72 @@ __global__ __launch_bounds__(kFinalizeThreads) void k_finalize_segments(const do
   }
 }
 
-// a6: network average, fp64 sum in worker order, rounded to the param dtype;
-// 16 bytes of columns per thread, the loads of 8 workers in flight at a time;
-// workgroups in tile order, `per` steps each.
-template <int DT>
-__global__ __launch_bounds__(256) void k_replica_mean(const void* x, int64_t ld, int n, int64_t P, int per,
-                                                      void* out) {
-  constexpr int V = DT == GASLOC_BF16 ? 8 : 4, R = 8;
-  const int64_t groups = (P + V - 1) / V;
-  const int64_t g0 = static_cast<int64_t>(blockIdx.x) * per * blockDim.x;
-  const int64_t g_end = groups - g0 < static_cast<int64_t>(per) * blockDim.x ? groups : g0 + per * blockDim.x;
-  for (int64_t gi = g0 + threadIdx.x; gi < g_end; gi += blockDim.x) {
-    const int64_t p = gi * V;
-    const int cnt = static_cast<int>(P - p < V ? P - p : V);
-    double s[V];
+// a / b for a finite b > 0 that is a small whole number, given r = 1 / b
+// rounded: the quotient a r corrected twice by its exact remainder is the
+// correctly rounded one (Markstein: from a quotient within one unit in the
+// last place, which the first correction gives, and a correctly rounded
+// reciprocal; compared with the division on 2.56e8 random sums for b = 1 to
+// 64), and the fixup restores zeros, infinities and NaN.  Half the instructions
+// of the general division.
+__device__ __forceinline__ double divide_by(double a, double b, double r) {
+  double q = a * r;
+  q = __builtin_fma(__builtin_fma(-b, q, a), r, q);
+  q = __builtin_fma(__builtin_fma(-b, q, a), r, q);
+  return __builtin_amdgcn_div_fixup(q, b, a);
+}
+
+// The averages of a thread's 4 columns (cnt of them in a ragged last group):
+// fp64 sums in worker order, rounded to the param dtype.
+template <int DT, bool TAIL>
+__device__ __forceinline__ void group_mean(const void* x, int64_t ld, int n, int64_t p, int cnt_tail, void* out) {
+  constexpr int V = kReduceVec, R = 8;
+  const int cnt = TAIL ? cnt_tail : V;
+  double s[V];
 #pragma unroll
-    for (int c = 0; c < V; ++c) s[c] = 0.0;
-    for (int i0 = 0; i0 < n; i0 += R) {
-      float v[R][V];
+  for (int c = 0; c < V; ++c) s[c] = 0.0;
+  for (int i0 = 0; i0 < n; i0 += R) {
+    float v[R][V];
 #pragma unroll
-      for (int r = 0; r < R; ++r) {
-        if (i0 + r >= n) break;
-        load_params<DT, V>(x, static_cast<int64_t>(i0 + r) * ld + p, cnt, v[r]);
-      }
-#pragma unroll
-      for (int r = 0; r < R; ++r) {
-        if (i0 + r >= n) break;
-#pragma unroll
-        for (int c = 0; c < V; ++c) s[c] += static_cast<double>(v[r][c]);
-      }
+    for (int r = 0; r < R; ++r) {
+      if (i0 + r >= n) break;
+      load_params<DT, V>(x, static_cast<int64_t>(i0 + r) * ld + p, cnt, v[r]);
     }
-    float mean[V], kept[V];
 #pragma unroll
-    for (int c = 0; c < V; ++c) mean[c] = static_cast<float>(s[c] / static_cast<double>(n));
-    store_params<DT, V>(out, p, cnt, mean, kept);
+    for (int r = 0; r < R; ++r) {
+      if (i0 + r >= n) break;
+#pragma unroll
+      for (int c = 0; c < V; ++c) s[c] += static_cast<double>(v[r][c]);
+    }
   }
+  const double b = static_cast<double>(n), r = 1.0 / b;
+  float mean[V], kept[V];
+#pragma unroll
+  for (int c = 0; c < V; ++c) mean[c] = static_cast<float>(divide_by(s[c], b, r));
+  store_params<DT, V>(out, p, cnt, mean, kept);
+}
+
+// a6: network average; 4 columns per thread, one step per workgroup (with
+// more, the next step's loads wait behind this one's store: n=16, P=50M bf16
+// 354 us with 8 steps, 318 with one, all else as before).
+template <int DT>
+__global__ __launch_bounds__(reduce_threads(DT)) void k_replica_mean(const void* x, int64_t ld, int n, int64_t P,
+                                                                     void* out) {
+  constexpr int V = kReduceVec;
+  const int64_t first = static_cast<int64_t>(blockIdx.x) * blockDim.x * V;
+  const int64_t p = first + threadIdx.x * V;
+  if (first + static_cast<int64_t>(blockDim.x) * V <= P)
+    group_mean<DT, false>(x, ld, n, p, V, out);
+  else if (p < P)
+    group_mean<DT, true>(x, ld, n, p, static_cast<int>(P - p < V ? P - p : V), out);
 }
 
 }  // namespace
 
 int consensus_error_blocks(int dtype, int64_t p_begin, int64_t p_end, int per) {
-  const int V = dtype == GASLOC_BF16 ? 8 : 4;
+  constexpr int V = kReduceVec;
   const int64_t base = p_begin - p_begin % V;
   const int64_t groups = (p_end - base + V - 1) / V;
-  const int64_t span = static_cast<int64_t>(per) * kReduceThreads;
+  const int64_t span = static_cast<int64_t>(per) * reduce_threads(dtype);
   const int64_t blocks = (groups + span - 1) / span;
   return static_cast<int>(blocks < 1 ? 1 : (blocks > (int64_t(1) << 30) ? (int64_t(1) << 30) : blocks));
 }
@@ -211,11 +258,11 @@ hipError_t launch_consensus_error(const void* x, int dtype, int64_t ld, int n, i
                                   int64_t p_end, int per, double* partials, hipStream_t stream) {
   const int blocks = consensus_error_blocks(dtype, p_begin, p_end, per);
   if (dtype == GASLOC_BF16)
-    hipLaunchKernelGGL((k_consensus_error<GASLOC_BF16>), dim3(blocks), dim3(kReduceThreads), 0, stream, x, ld,
-                       n, p_begin, p_end, per, partials);
+    hipLaunchKernelGGL((k_consensus_error<GASLOC_BF16>), dim3(blocks), dim3(reduce_threads(GASLOC_BF16)), 0, stream, x,
+                       ld, n, p_begin, p_end, per, partials);
   else
-    hipLaunchKernelGGL((k_consensus_error<GASLOC_F32>), dim3(blocks), dim3(kReduceThreads), 0, stream, x, ld, n,
-                       p_begin, p_end, per, partials);
+    hipLaunchKernelGGL((k_consensus_error<GASLOC_F32>), dim3(blocks), dim3(reduce_threads(GASLOC_F32)), 0, stream, x,
+                       ld, n, p_begin, p_end, per, partials);
   return hipGetLastError();
 }
 
@@ -248,15 +295,15 @@ hipError_t launch_finalize2_large(const double* a, const double* b, int count, d
   return launch_finalize2(seg, seg + segments, segments, out, stream);
 }
 
-hipError_t launch_replica_mean(const void* x, int dtype, int64_t ld, int n, int64_t P, int per, void* out,
+hipError_t launch_replica_mean(const void* x, int dtype, int64_t ld, int n, int64_t P, void* out,
                                hipStream_t stream) {
-  const int blocks = consensus_error_blocks(dtype, 0, P, per);
+  const int blocks = consensus_error_blocks(dtype, 0, P, 1);
   if (dtype == GASLOC_BF16)
-    hipLaunchKernelGGL((k_replica_mean<GASLOC_BF16>), dim3(blocks), dim3(kReduceThreads), 0, stream, x, ld, n, P,
-                       per, out);
+    hipLaunchKernelGGL((k_replica_mean<GASLOC_BF16>), dim3(blocks), dim3(reduce_threads(GASLOC_BF16)), 0, stream, x,
+                       ld, n, P, out);
   else
-    hipLaunchKernelGGL((k_replica_mean<GASLOC_F32>), dim3(blocks), dim3(kReduceThreads), 0, stream, x, ld, n, P,
-                       per, out);
+    hipLaunchKernelGGL((k_replica_mean<GASLOC_F32>), dim3(blocks), dim3(reduce_threads(GASLOC_F32)), 0, stream, x,
+                       ld, n, P, out);
   return hipGetLastError();
 }
 
@@ -307,7 +354,7 @@ extern "C" gasloc_status gasloc_consensus_error_cols_noalloc(const void* x, int3
     return noalloc_fail(GASLOC_EINVAL, "need 0 <= p_begin <= p_end <= ld and p_end < 2^31");
   const int blocks = gasloc::consensus_error_blocks(param_dtype, p_begin, p_end, kNoAllocPer);
   if (blocks > kNoAllocPartials) {
-    const int64_t most = int64_t(kNoAllocPartials) * kNoAllocPer * gasloc::kReduceThreads * (elem == 2 ? 8 : 4);
+    const int64_t most = int64_t(kNoAllocPartials) * kNoAllocPer * gasloc::reduce_step(param_dtype);
     return noalloc_fail(GASLOC_EINVAL, "column range longer than the scratch allows (at most " + std::to_string(most) +
                                            " columns of this dtype per call; split the range and add the results)");
   }

@@ -430,8 +430,8 @@ gasloc::LaunchShape pick_tile_shape(const gasloc_ctx& c, bool rows_equal, gasloc
 // Steps of the standalone consensus error per workgroup: 8 (as the round
 // kernels), fewer on short ranges so that every CU still gets 16 workgroups.
 int reduce_per(const gasloc_ctx& c, int64_t p0, int64_t p1) {
-  const int V = c.hp.param_dtype == GASLOC_BF16 ? 8 : 4;
-  const int64_t steps = ((p1 - p0 + V) / V + gasloc::kReduceThreads - 1) / gasloc::kReduceThreads;
+  const int step = gasloc::reduce_step(c.hp.param_dtype);
+  const int64_t steps = (p1 - p0 + gasloc::kReduceVec + step - 1) / step;
   return static_cast<int>(std::min<int64_t>(8, std::max<int64_t>(1, steps / (16 * int64_t(c.cus)))));
 }
 
@@ -879,8 +879,7 @@ gasloc_status gasloc_replica_mean(gasloc_ctx* c, void* out) {
   if (c->failed) return fail(c, GASLOC_ESTATE, "context unusable after a device error: " + c->err);
   if (!out || !aligned16(out)) return fail(c, GASLOC_EINVAL, "out must be non-NULL and 16-byte aligned");
   DeviceGuard guard(c->device);
-  HIP_TRY(c, gasloc::launch_replica_mean(c->buf.x, c->hp.param_dtype, c->buf.ld, c->n, c->P,
-                                         reduce_per(*c, 0, c->P), out, c->stream));
+  HIP_TRY(c, gasloc::launch_replica_mean(c->buf.x, c->hp.param_dtype, c->buf.ld, c->n, c->P, out, c->stream));
   return GASLOC_OK;
 }
 

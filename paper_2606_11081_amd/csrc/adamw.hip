@@ -7,6 +7,10 @@
 namespace gasloc {
 namespace {
 
+// A CU's 160 KiB of LDS in granules of 1280 bytes hold six of these.
+constexpr size_t kTilesPerCu = 6;
+constexpr size_t kTileLds = (160 * 1024 / kTilesPerCu) / 1280 * 1280;
+
 // One workgroup per tile of 256 x 4 consecutive columns of one active worker:
 // grid (tiles, n_active), tiles = ceil(P / 1024); slot blockIdx.y updates
 // worker rep[slot].  The grid is not persistent: workgroups are dispatched in
@@ -16,6 +20,16 @@ namespace {
 // MI355X that spread the accesses over the whole row and made the launch's
 // speed depend on where the buffers were placed: 25.4-30.1 ms at n = 16,
 // P = 350M, against 24.3-26.0 ms for the tiles in the same processes.)
+//
+// Concurrency is bounded on purpose: each thread waits for one stream's load
+// before the next (the per-lane test of the ragged end does that), and
+// kTilesPerCu workgroups share a CU, by LDS that nothing uses.  With more
+// tiles in flight the seven streams' windows grow and HBM pages conflict: n=16,
+// P=100M fp32, three buffer sets, 8 workgroups per CU 7.39 / 7.34 / 7.50 ms, 7
+// 7.29 / 7.19 / 7.38, 6 7.15 / 7.07 / 7.22 (6.3 TB/s), 5 7.48 / 7.45 / 7.65, 3
+// 8.61.  Without the per-lane test, all loads at once: 8 per CU 7.71 / 7.79 /
+// 7.78, 3 per CU 7.15 / 7.02 / 7.48.  Workgroups of 512 threads 7.26 ms and
+// more, of 128 threads 7.09 to 7.42.
 template <int DT>
 __global__ __launch_bounds__(256) void k_local_adamw(AdamArgs a) {
   constexpr int V = 4;
@@ -47,9 +61,9 @@ hipError_t launch_local_adamw(const AdamArgs& a, int dtype, hipStream_t stream) 
   constexpr int64_t kTile = 256 * 4;  // columns per workgroup
   const dim3 grid(static_cast<unsigned>((a.P + kTile - 1) / kTile), a.n_active);
   if (dtype == GASLOC_BF16)
-    hipLaunchKernelGGL((k_local_adamw<GASLOC_BF16>), grid, dim3(256), 0, stream, a);
+    hipLaunchKernelGGL((k_local_adamw<GASLOC_BF16>), grid, dim3(256), kTileLds, stream, a);
   else
-    hipLaunchKernelGGL((k_local_adamw<GASLOC_F32>), grid, dim3(256), 0, stream, a);
+    hipLaunchKernelGGL((k_local_adamw<GASLOC_F32>), grid, dim3(256), kTileLds, stream, a);
   return hipGetLastError();
 }
 

@@ -35,6 +35,8 @@ namespace {
 typedef const __attribute__((address_space(4))) int32_t uniform_i32;
 typedef const __attribute__((address_space(4))) float uniform_f32;
 
+constexpr int kWaitVector = 0x0f70;  // s_waitcnt vmcnt(0); the other counters are not waited for
+
 // What a worker's row needs after the barrier, by form: EQ the consensus
 // momentum term; ALG1 x and u; DAdam y - x; Local-DAdam x, y and u.
 template <int V, int FORM>
@@ -43,7 +45,17 @@ struct RowKept {
   float v[count][V];
 };
 
-// The streams of one worker as loaded.
+// The streams of one worker as loaded (the forms other than EQ: y and u only
+// where the worker has them).
+//
+// The copy of x into y below makes the compiler wait for x before it issues
+// the worker's other loads, and its conservative waits past the branches wait
+// for stores as well.  The other forms avoid both (tile_round), which took 1
+// to 4% off: n=22, P=17.8M Local-DAdam 3.41 -> 3.31 ms, n=16, P=50M bf16
+// Algorithm 1 4.34 -> 4.23.  The EQ form, with more streams, is 1 to 3% faster
+// as it is (n=12, P=50M ring 5.74 against 5.93 ms, n=4, P=67M 2.08 against
+// 2.12, n=8, P=124M 7.87 against 7.98): more loads in flight than HBM needs
+// make its pages conflict.
 template <int V, bool FUSED, int FORM>
 struct WorkerLoads {
   float x[V], y[V], u[V], zp[V];
@@ -59,7 +71,7 @@ __device__ __forceinline__ void tile_load(const GossipArgs& a, int i, int64_t ti
   load_params<DT, V>(static_cast<const char*>(a.x) + row * sp, at, cnt, w.x);
   if ((a.stepped >> i) & 1ull) {
     load_params<DT, V>(static_cast<const char*>(a.y) + row * sp, at, cnt, w.y);
-  } else {
+  } else if constexpr (kEq) {
 #pragma unroll
     for (int c = 0; c < V; ++c) w.y[c] = w.x[c];
   }
@@ -72,7 +84,7 @@ __device__ __forceinline__ void tile_load(const GossipArgs& a, int i, int64_t ti
   }
   if (FORM != GASLOC_FORM_DADAM && a.use_u) {
     load_f32<V>(a.u + row + at, cnt, w.u);
-  } else {
+  } else if constexpr (kEq) {
 #pragma unroll
     for (int c = 0; c < V; ++c) w.u[c] = 0.0f;
   }
@@ -84,6 +96,15 @@ __device__ __forceinline__ void tile_produce(const GossipArgs& a, int i, int64_t
                                              WorkerLoads<V, FUSED, FORM>& w, float* slot, RowKept<V, FORM>& kept,
                                              double& pg) {
   const int64_t row = static_cast<int64_t>(i) * a.ld + tile0;  // uniform
+  if constexpr (FORM != GASLOC_FORM_EQ) {
+    const bool stepped = (a.stepped >> i) & 1ull;
+    const bool with_u = FORM != GASLOC_FORM_DADAM && a.use_u;
+#pragma unroll
+    for (int c = 0; c < V; ++c) {
+      w.y[c] = stepped ? w.y[c] : w.x[c];
+      w.u[c] = with_u ? w.u[c] : 0.0f;
+    }
+  }
   if constexpr (FUSED) {
     if ((a.active >> i) & 1ull) {
       const float s1 = a.s1[i], c2 = a.c2[i];
@@ -91,8 +112,10 @@ __device__ __forceinline__ void tile_produce(const GossipArgs& a, int i, int64_t
       for (int c = 0; c < V; ++c)
         w.y[c] = as_stored<DT>(adamw_element(w.y[c], w.g[c], w.m[c], w.v[c], a.c_wd, a.b1, a.omb1, a.b2, a.omb2,
                                              a.eps, s1, c2));
-      store_f32<V>(a.m + row + at, cnt, w.m);
-      store_f32<V>(a.v + row + at, cnt, w.v);
+      if constexpr (FORM == GASLOC_FORM_EQ) {
+        store_f32<V>(a.m + row + at, cnt, w.m);
+        store_f32<V>(a.v + row + at, cnt, w.v);
+      }
     }
   }
 #pragma unroll
@@ -220,10 +243,23 @@ __device__ __forceinline__ void tile_round(const GossipArgs& a, unsigned char* l
       const int i = wave + (k0 + b) * waves;
       if (i < n) tile_load<DT, V, FUSED, FORM>(a, i, tile0, at, cnt, w[b]);
     }
+    // One wait for the batch, after which no load is pending on any path
+    if constexpr (FORM != GASLOC_FORM_EQ) __builtin_amdgcn_s_waitcnt(kWaitVector);
 #pragma unroll
     for (int b = 0; b < B; ++b) {
       const int i = wave + (k0 + b) * waves;
       if (i < n) tile_produce<DT, V, FUSED, FORM>(a, i, tile0, at, cnt, w[b], zs + i * C + at, kept[k0 + b], pg);
+    }
+    if constexpr (FUSED && FORM != GASLOC_FORM_EQ) {  // the batch's moments, once all its values are computed
+#pragma unroll
+      for (int b = 0; b < B; ++b) {
+        const int i = wave + (k0 + b) * waves;
+        if (i < n && ((a.active >> i) & 1ull)) {
+          const int64_t e = static_cast<int64_t>(i) * a.ld + tile0 + at;
+          store_f32<V>(a.m + e, cnt, w[b].m);
+          store_f32<V>(a.v + e, cnt, w[b].v);
+        }
+      }
     }
   }
   __syncthreads();  // every worker's value is in its slot

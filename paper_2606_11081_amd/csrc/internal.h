@@ -169,6 +169,8 @@ hipError_t launch_finalize2_large(const double* a, const double* b, int count, d
 // *out = the sum of a[0..count), count <= kMaxPartials, in the same
 // segmented order (seg: at least ceil(count / kFinalizeSegment) doubles).
 hipError_t launch_finalize_large(const double* a, int count, double* seg, double* out, hipStream_t stream);
+// Zeros columns [0, P) of each of the n rows of x.
+hipError_t launch_zero_rows(float* x, int64_t ld, int n, int64_t P, hipStream_t stream);
 // The network average of columns [0, P), one step per workgroup.
 hipError_t launch_replica_mean(const void* x, int dtype, int64_t ld, int n, int64_t P, void* out,
                                hipStream_t stream);

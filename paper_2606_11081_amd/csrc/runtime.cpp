@@ -777,9 +777,7 @@ gasloc_status gasloc_init(int32_t n, int64_t P, const gasloc_topology* topology,
   // each row only (the row padding is the caller's)
   for (float* p : {b.m, b.v, b.u, b.zp}) {
     if (!p) continue;
-    if ((e = hipMemset2DAsync(p, sizeof(float) * static_cast<size_t>(b.ld), 0, sizeof(float) * static_cast<size_t>(P),
-                              static_cast<size_t>(n), c->stream)) != hipSuccess)
-      return init_fail(e, "hipMemset2DAsync");
+    if ((e = gasloc::launch_zero_rows(p, b.ld, n, P, c->stream)) != hipSuccess) return init_fail(e, "zero state");
   }
   *out = c;
   return GASLOC_OK;

@@ -98,10 +98,15 @@ struct GossipArgs {
   int32_t slots;
 
   // k_gossip_tile only: byte offsets in LDS of the stored rows (0: they take
-  // the slots' place) and of the shared neighbour sums; whether every row
-  // holds the entries of row 0
+  // the slots' place) and of the shared neighbour sums; if every row holds the
+  // entries of row 0 and the form sums them the same way, those entries (else
+  // sum_entries is 0 and the rows are read from the CSR).  As arguments they
+  // belong to the launch: one recorded in a graph keeps them, whatever the
+  // context's CSR holds when it is replayed.
   int32_t kept_off, sums_off;
-  int32_t rows_equal;
+  int32_t sum_entries;
+  int32_t sum_col[kMaxReplicas];
+  float sum_w[kMaxReplicas];
 
   // Fused last local step (the fused kernel only): every worker i with bit i
   // of `active` first takes one AdamW step from its live iterate; the new

@@ -264,12 +264,11 @@ __device__ __forceinline__ void tile_round(const GossipArgs& a, unsigned char* l
   }
   __syncthreads();  // every worker's value is in its slot
   constexpr bool kSums = FORM == GASLOC_FORM_EQ || FORM == GASLOC_FORM_DADAM;
-  const bool shared = kSums && a.rows_equal;
+  const bool shared = kSums && a.sum_entries > 0;
   if (shared) {
-    const int entries = rp[1];
     for (int c = threadIdx.x; c < C; c += blockDim.x) {
       float s = 0.0f;
-      for (int k = 0; k < entries; ++k) s = s + val[k] * zs[col[k] * C + c];
+      for (int k = 0; k < a.sum_entries; ++k) s = s + a.sum_w[k] * zs[a.sum_col[k] * C + c];
       sums[c] = s;
     }
     __syncthreads();

@@ -393,7 +393,7 @@ RoundKernel pick_round_kernel() {
 // The stored rows get LDS of their own up to 32 workers; beyond, they take the
 // slots' place after one more barrier, so that two workgroups fit a CU (n=64,
 // P=25M matching: 11.57 ms with LDS of their own, 9.42 ms in place).
-gasloc::LaunchShape pick_tile_shape(const gasloc_ctx& c, bool rows_equal, gasloc::GossipArgs* a, size_t* lds) {
+gasloc::LaunchShape pick_tile_shape(const gasloc_ctx& c, gasloc::GossipArgs* a, size_t* lds) {
   constexpr int64_t kCols = 64 * gasloc::kTileVec;
   const int64_t tiles = (c.P + kCols - 1) / kCols;
   const int fewest = c.n <= 16 ? 1 : (c.n <= 32 ? 2 : 4);
@@ -419,8 +419,7 @@ gasloc::LaunchShape pick_tile_shape(const gasloc_ctx& c, bool rows_equal, gasloc
     end += slots * param_bytes(c.hp.param_dtype);
   }
   a->sums_off = static_cast<int32_t>(end);
-  a->rows_equal = rows_equal;
-  if (rows_equal) end += kCols * sizeof(float);
+  if (a->sum_entries > 0) end += kCols * sizeof(float);
   *lds = end;
   const int waves = (c.n + per_wave - 1) / per_wave;
   return gasloc::LaunchShape{gasloc::kTileVec, 64 * waves, static_cast<int>((tiles + per - 1) / per), per_wave,
@@ -553,7 +552,15 @@ gasloc_status run_round(gasloc_ctx* c, const gasloc_csr* W, uint64_t t, const St
   const bool tile = kernel == RoundKernel::kTile;
   gasloc::GossipArgs a{};
   if (tile) {
-    shape = pick_tile_shape(*c, rows_all_equal(c->n, rp, col, val), &a, &lds);
+    // one sum for all rows where they are equal and it does not depend on the
+    // row: its entries go with the launch, and the round needs no CSR
+    if ((c->hp.round_form == GASLOC_FORM_EQ || c->hp.round_form == GASLOC_FORM_DADAM) &&
+        rows_all_equal(c->n, rp, col, val)) {
+      a.sum_entries = rp[1];
+      std::memcpy(a.sum_col, col, sizeof(int32_t) * static_cast<size_t>(rp[1]));
+      std::memcpy(a.sum_w, val, sizeof(float) * static_cast<size_t>(rp[1]));
+    }
+    shape = pick_tile_shape(*c, &a, &lds);
     lds += gasloc::kStaticLds;
   } else if (planned) {
     // 4 columns per thread when the plan needs few slots (n=64 1-Peer: 10.7-
@@ -598,8 +605,10 @@ gasloc_status run_round(gasloc_ctx* c, const gasloc_csr* W, uint64_t t, const St
                                   &err))
       return fail(c, GASLOC_EINVAL, err);
   }
-  gasloc_status st = planned ? upload_plan(c, c->plan_ops) : upload_csr(c, rp, col, val, nnz);
-  if (st != GASLOC_OK) return st;
+  if (a.sum_entries == 0) {
+    gasloc_status st = planned ? upload_plan(c, c->plan_ops) : upload_csr(c, rp, col, val, nnz);
+    if (st != GASLOC_OK) return st;
+  }
 
   a.x = c->buf.x;
   a.y = c->buf.y;

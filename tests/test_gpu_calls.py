@@ -1,0 +1,76 @@
+"""Calls around a round on the GPU: a round recorded in a HIP graph, the
+consensus error reduced afresh, calls after a failed HIP call of the program's
+own."""
+import numpy as np
+import pytest
+
+import gasloc_inputs as gi
+
+pytestmark = pytest.mark.gpu
+
+
+def _context(n, P, form, dtype, gamma, stream):
+    import paper_2606_11081_amd as g
+
+    return g.GASLoC(n, P, topology="complete", param_dtype=dtype, outer_lr=gi.OUTER_LR,
+                    outer_momentum=gi.OUTER_MOMENTUM, consensus_momentum=gamma, round_form=form, stream=stream)
+
+
+def _bits(t):
+    import torch
+
+    return t.contiguous().view(torch.int16 if t.dtype == torch.bfloat16 else torch.int32)
+
+
+@pytest.mark.parametrize("n,P,form,dtype,gamma", [(8, 1_500, "eq", "f32", 0.1), (40, 300, "eq", "bf16", 0.0),
+                                                  (17, 513, "dadam", "f32", 0.0)])
+def test_recorded_complete_round_keeps_its_graph(n, P, form, dtype, gamma):
+    """Replays of a recorded round whose rows are all equal mix with the
+    recorded entries, also after rounds with another graph on the context."""
+    import torch
+
+    print("case recorded complete round n=%d P=%d %s %s" % (n, P, form, dtype), flush=True)
+    stream = torch.cuda.Stream()
+    with torch.cuda.stream(stream):
+        run = _context(n, P, form, dtype, gamma, stream)
+        ref = _context(n, P, form, dtype, gamma, stream)
+        gen = torch.Generator(device="cuda")
+        gen.manual_seed(n * P)
+        names = [k for k in ("x", "y", "m", "v", "u", "zp") if run.bufs[k] is not None]
+        start = {k: torch.empty((n, P), device="cuda").normal_(0.0, 0.02, generator=gen).to(run.bufs[k].dtype)
+                 for k in names}
+        ring = (np.arange(0, 3 * n + 1, 3, dtype=np.int32),
+                np.concatenate([np.sort([(i - 1) % n, i, (i + 1) % n]) for i in range(n)]).astype(np.int32),
+                np.full(3 * n, 1.0 / 3.0, np.float32))
+
+        def restore(r):
+            for k in names:
+                r.bufs[k][:, :P].copy_(start[k])
+            r.set_counters(np.full(n, 7, np.int64), np.ones(n, np.uint8), 3)
+
+        restore(ref)
+        ref.gossip_round(3)
+        want = {k: _bits(ref.bufs[k][:, :P]) for k in names}
+        stats = (ref.consensus_error(), ref.pseudo_gradient_sq())
+
+        run.gossip_round(3)  # warm-up
+        restore(run)
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=stream):
+            run.gossip_round(3)
+        for replay in range(3):
+            restore(run)
+            graph.replay()
+            for k in names:
+                assert torch.equal(_bits(run.bufs[k][:, :P]), want[k]), (replay, k)
+            run.gossip_round(4, ring)  # eager work between the replays
+            stream.synchronize()
+        restore(run)
+        graph.replay()
+        assert run.pseudo_gradient_sq() == stats[1]
+        run.gossip_round(3)
+        restore(run)
+        run.gossip_round(3)
+        assert (run.consensus_error(), run.pseudo_gradient_sq()) == stats
+        run.close()
+        ref.close()

@@ -84,7 +84,7 @@ __device__ __forceinline__ double group_error(const void* x, int64_t ld, int n, 
       for (int c = 0; c < V; ++c) {
         const double d = static_cast<double>(v[r][c]) - shift[c];
         s[c] += d;
-        q[c] = __builtin_fma(d, d, q[c]);
+        q[c] += d * d;
       }
     }
   }

@@ -74,3 +74,37 @@ def test_recorded_complete_round_keeps_its_graph(n, P, form, dtype, gamma):
         assert (run.consensus_error(), run.pseudo_gradient_sq()) == stats
         run.close()
         ref.close()
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("n", [2, 11, 33, 64])
+def test_consensus_error_afresh_is_the_rounds(n, dtype):
+    """One column: the error that a round keeps, the one reduced afresh and the
+    stated arithmetic (deviations from worker 0, fp64, each operation rounded
+    on its own, workers in order) are the same number."""
+    import torch
+
+    print("case consensus error afresh n=%d %s" % (n, dtype), flush=True)
+    import paper_2606_11081_amd as g
+
+    run = g.GASLoC(n, 1, topology="ring", param_dtype=dtype, outer_lr=gi.OUTER_LR, outer_momentum=gi.OUTER_MOMENTUM,
+                   consensus_momentum=0.1)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(n)
+    grads = torch.empty((n, run.ld), device="cuda")
+    run.x.normal_(0.0, 1.0, generator=gen)
+    out = torch.empty(1, dtype=torch.float64, device="cuda")
+    for t in range(12):
+        grads.normal_(0.0, 1.0, generator=gen)
+        run.local_step_gossip_round(grads, gi.LOCAL_LR, t)
+        fused = run.consensus_error()
+        afresh = run.consensus_error_cols(0, 1)
+        g.gasloc_consensus_error_cols_noalloc(run.x, dtype, n, run.ld, 0, 1, out)
+        x = run.x[:, 0].double().cpu().numpy()
+        s = q = np.float64(0.0)
+        for v in x[1:]:
+            d = v - x[0]
+            s += d
+            q += d * d
+        assert fused == afresh == float(out) == q - s * s * (1.0 / np.float64(n)), t
+    run.close()

@@ -60,11 +60,8 @@ __global__ __launch_bounds__(256) void k_local_adamw(AdamArgs a) {
 hipError_t launch_local_adamw(const AdamArgs& a, int dtype, hipStream_t stream) {
   constexpr int64_t kTile = 256 * 4;  // columns per workgroup
   const dim3 grid(static_cast<unsigned>((a.P + kTile - 1) / kTile), a.n_active);
-  if (dtype == GASLOC_BF16)
-    hipLaunchKernelGGL((k_local_adamw<GASLOC_BF16>), grid, dim3(256), kTileLds, stream, a);
-  else
-    hipLaunchKernelGGL((k_local_adamw<GASLOC_F32>), grid, dim3(256), kTileLds, stream, a);
-  return hipGetLastError();
+  return launch_kernel(dtype == GASLOC_BF16 ? k_local_adamw<GASLOC_BF16> : k_local_adamw<GASLOC_F32>, grid, 256,
+                       kTileLds, stream, a);
 }
 
 }  // namespace gasloc

@@ -288,13 +288,25 @@ __device__ __forceinline__ float outer_step(float base, float d, float& u, float
   return base - eta * step;
 }
 
+// Launches `kernel` and returns the status of this launch alone: the thread's
+// last error may be one that the calling program has already dealt with.
+template <typename T>
+struct Same {
+  typedef T type;
+};
+template <typename... P>
+inline hipError_t launch_kernel(void (*kernel)(P...), dim3 grid, int threads, size_t lds, hipStream_t stream,
+                                typename Same<P>::type... args) {
+  void* ptrs[] = {&args...};
+  return hipLaunchKernel(reinterpret_cast<const void*>(kernel), grid, dim3(threads), ptrs, lds, stream);
+}
+
 // Launches `kernel` with the round arguments.
 inline hipError_t launch_round_args(const void* kernel, const GossipArgs& a, const LaunchShape& s, size_t lds,
                                     hipStream_t stream) {
   GossipArgs arg = a;
   void* args[] = {&arg};
-  const hipError_t e = hipLaunchKernel(kernel, dim3(s.blocks), dim3(s.threads), args, lds, stream);
-  return e != hipSuccess ? e : hipGetLastError();
+  return hipLaunchKernel(kernel, dim3(s.blocks), dim3(s.threads), args, lds, stream);
 }
 
 }  // namespace

@@ -269,60 +269,46 @@ int consensus_error_blocks(int dtype, int64_t p_begin, int64_t p_end, int per) {
 hipError_t launch_consensus_error(const void* x, int dtype, int64_t ld, int n, int64_t p_begin,
                                   int64_t p_end, int per, double* partials, hipStream_t stream) {
   const int blocks = consensus_error_blocks(dtype, p_begin, p_end, per);
-  if (dtype == GASLOC_BF16)
-    hipLaunchKernelGGL((k_consensus_error<GASLOC_BF16>), dim3(blocks), dim3(reduce_threads(GASLOC_BF16)), 0, stream, x,
-                       ld, n, p_begin, p_end, per, partials);
-  else
-    hipLaunchKernelGGL((k_consensus_error<GASLOC_F32>), dim3(blocks), dim3(reduce_threads(GASLOC_F32)), 0, stream, x,
-                       ld, n, p_begin, p_end, per, partials);
-  return hipGetLastError();
+  return launch_kernel(dtype == GASLOC_BF16 ? k_consensus_error<GASLOC_BF16> : k_consensus_error<GASLOC_F32>,
+                       dim3(blocks), reduce_threads(dtype), 0, stream, x, ld, n, p_begin, p_end, per, partials);
 }
 
 hipError_t launch_finalize_large(const double* a, int count, double* seg, double* out, hipStream_t stream) {
   if (count <= kFinalizeSegment) return launch_finalize(a, count, out, stream);
   const int segments = (count + kFinalizeSegment - 1) / kFinalizeSegment;
-  hipLaunchKernelGGL(k_finalize_segments, dim3(segments), dim3(kFinalizeThreads), 0, stream, a, nullptr, count, seg);
-  const hipError_t e = hipGetLastError();
+  const hipError_t e =
+      launch_kernel(k_finalize_segments, dim3(segments), kFinalizeThreads, 0, stream, a, nullptr, count, seg);
   if (e != hipSuccess) return e;
   return launch_finalize(seg, segments, out, stream);
 }
 
 hipError_t launch_finalize(const double* partials, int count, double* out, hipStream_t stream) {
-  hipLaunchKernelGGL(k_finalize, dim3(1), dim3(kFinalizeThreads), 0, stream, partials, count, out);
-  return hipGetLastError();
+  return launch_kernel(k_finalize, dim3(1), kFinalizeThreads, 0, stream, partials, count, out);
 }
 
 hipError_t launch_finalize2(const double* a, const double* b, int count, double* out, hipStream_t stream) {
-  hipLaunchKernelGGL(k_finalize2, dim3(1), dim3(kFinalizeThreads), 0, stream, a, b, count, out);
-  return hipGetLastError();
+  return launch_kernel(k_finalize2, dim3(1), kFinalizeThreads, 0, stream, a, b, count, out);
 }
 
 hipError_t launch_finalize2_large(const double* a, const double* b, int count, double* seg, double* out,
                                   hipStream_t stream) {
   if (count <= kFinalizeSegment) return launch_finalize2(a, b, count, out, stream);
   const int segments = (count + kFinalizeSegment - 1) / kFinalizeSegment;
-  hipLaunchKernelGGL(k_finalize_segments, dim3(segments), dim3(kFinalizeThreads), 0, stream, a, b, count, seg);
-  const hipError_t e = hipGetLastError();
+  const hipError_t e = launch_kernel(k_finalize_segments, dim3(segments), kFinalizeThreads, 0, stream, a, b, count, seg);
   if (e != hipSuccess) return e;
   return launch_finalize2(seg, seg + segments, segments, out, stream);
 }
 
 hipError_t launch_zero_rows(float* x, int64_t ld, int n, int64_t P, hipStream_t stream) {
   const dim3 grid(static_cast<unsigned>((P + 1023) / 1024), static_cast<unsigned>(n));
-  hipLaunchKernelGGL(k_zero_rows, grid, dim3(256), 0, stream, x, ld, P);
-  return hipGetLastError();
+  return launch_kernel(k_zero_rows, grid, 256, 0, stream, x, ld, P);
 }
 
 hipError_t launch_replica_mean(const void* x, int dtype, int64_t ld, int n, int64_t P, void* out,
                                hipStream_t stream) {
   const int blocks = consensus_error_blocks(dtype, 0, P, 1);
-  if (dtype == GASLOC_BF16)
-    hipLaunchKernelGGL((k_replica_mean<GASLOC_BF16>), dim3(blocks), dim3(reduce_threads(GASLOC_BF16)), 0, stream, x,
-                       ld, n, P, out);
-  else
-    hipLaunchKernelGGL((k_replica_mean<GASLOC_F32>), dim3(blocks), dim3(reduce_threads(GASLOC_F32)), 0, stream, x,
-                       ld, n, P, out);
-  return hipGetLastError();
+  return launch_kernel(dtype == GASLOC_BF16 ? k_replica_mean<GASLOC_BF16> : k_replica_mean<GASLOC_F32>, dim3(blocks),
+                       reduce_threads(dtype), 0, stream, x, ld, n, P, out);
 }
 
 }  // namespace gasloc

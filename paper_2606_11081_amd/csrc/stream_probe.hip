@@ -53,9 +53,7 @@ template <int R32, int R16, int W32, int W16>
 hipError_t launch_probe(const ProbeArgs& a, int threads, hipStream_t stream) {
   const int64_t tile = 4 * static_cast<int64_t>(threads);
   const int64_t tiles = (a.count + tile - 1) / tile;
-  hipLaunchKernelGGL((k_stream_probe<R32, R16, W32, W16>), dim3(static_cast<unsigned>(tiles)), dim3(threads), 0,
-                     stream, a);
-  return hipGetLastError();
+  return launch_kernel(k_stream_probe<R32, R16, W32, W16>, dim3(static_cast<unsigned>(tiles)), threads, 0, stream, a);
 }
 
 }  // namespace

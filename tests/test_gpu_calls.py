@@ -108,3 +108,40 @@ def test_consensus_error_afresh_is_the_rounds(n, dtype):
             q += d * d
         assert fused == afresh == float(out) == q - s * s * (1.0 / np.float64(n)), t
     run.close()
+
+
+def test_calls_after_a_failed_hip_call_of_the_program():
+    """A HIP call of the program's own that failed, and whose error the program
+    has handled, fails no call of the library and is still there to be read."""
+    import torch
+
+    print("case calls after a failed HIP call", flush=True)
+    import paper_2606_11081_amd as g
+
+    n, P = 4, 1_000
+    lib = g.library()  # its symbols and those of the HIP runtime it is linked to
+    x = torch.zeros(n, P, device="cuda")
+    out = torch.empty(1, dtype=torch.float64, device="cuda")
+    grads = torch.ones(n, g.padded_ld(P, "f32"), device="cuda")
+    mean = torch.empty(P, device="cuda")
+    bufs = g.alloc_buffers(n, P)
+    bufs["x"].zero_()
+    torch.cuda.synchronize()
+    lib.hipGetLastError()
+    failed = lib.hipSetDevice(1 << 20)  # no such GPU: refused by the runtime, nothing reaches the device
+    assert failed != 0
+    try:
+        ctx = g.gasloc_init(n, P, g.make_topology_struct("complete", 0, 3), g.make_hparams(), bufs["x"], bufs["y"],
+                            bufs["m"], bufs["v"], bufs["u"], bufs["zp"], bufs["ld"],
+                            torch.cuda.current_stream().cuda_stream)
+        g.gasloc_local_step(ctx, grads, grads.shape[1], None, 1e-3)
+        g.gasloc_gossip_round(ctx, None, 0)
+        assert g.gasloc_consensus_error(ctx) == 0.0
+        assert g.gasloc_consensus_error_cols(ctx, 0, P) == 0.0
+        g.gasloc_replica_mean(ctx, mean)
+        g.gasloc_destroy(ctx)
+        g.gasloc_consensus_error_cols_noalloc(x, "f32", n, P, 0, P, out)
+    finally:
+        left = lib.hipGetLastError()  # cleared for the tests that follow
+    assert left in (0, failed)
+    assert float(out) == 0.0

@@ -350,11 +350,12 @@ def padded_ld(P, param_dtype):
     return (P + line - 1) // line * line
 
 
-def alloc_buffers(n, P, param_dtype="f32", device="cuda", with_u=True, with_zp=True):
-    """torch tensors x, y, m, v, u, zp of shape [n, ld] (u / zp None when not wanted)."""
+def alloc_buffers(n, P, param_dtype="f32", device="cuda", with_u=True, with_zp=True, ld=None):
+    """torch tensors x, y, m, v, u, zp of shape [n, ld] (u / zp None when not wanted);
+    ld: the row length, padded_ld unless given."""
     import torch
 
-    ld = padded_ld(P, param_dtype)
+    ld = padded_ld(P, param_dtype) if ld is None else int(ld)
     pdt = torch.bfloat16 if param_dtype in ("bf16", GASLOC_BF16) else torch.float32
     x = torch.empty((n, ld), dtype=pdt, device=device)
     y = torch.empty((n, ld), dtype=pdt, device=device)
@@ -366,17 +367,21 @@ def alloc_buffers(n, P, param_dtype="f32", device="cuda", with_u=True, with_zp=T
 
 
 class GASLoC:
-    """Owns one context plus its torch buffers; methods are the ABI calls."""
+    """Owns one context plus its torch buffers; methods are the ABI calls.
+
+    ld: the row length of the buffers (padded_ld unless given).  A state that
+    was saved as whole [n, ld] buffers is restored into buffers of that row
+    length, GASLoC(..., ld=saved.shape[1]), or column by column, [:, :P]."""
 
     def __init__(self, n, P, topology="ring", seed=0, degree=3, param_dtype="f32", device="cuda",
-                 stream=None, admissible=None, **hp):
+                 stream=None, admissible=None, ld=None, **hp):
         import torch
 
         self.n, self.P, self.param_dtype = int(n), int(P), param_dtype
         hpar = make_hparams(param_dtype=param_dtype, **hp)
         self.bufs = alloc_buffers(n, P, param_dtype, device,
                                   with_u=hpar.outer_momentum != 0.0 and hpar.round_form != ROUND_FORM["dadam"],
-                                  with_zp=hpar.consensus_momentum != 0.0)
+                                  with_zp=hpar.consensus_momentum != 0.0, ld=ld)
         self.ld = self.bufs["ld"]
         self.stream = torch.cuda.current_stream(device) if stream is None else stream
         b = self.bufs
@@ -425,7 +430,7 @@ class GASLoC:
         return gasloc_get_counters(self.ctx, self.n)
 
     def set_counters(self, k, stepped, rounds_done):
-        """Restore the counters of a checkpoint (with the [n, ld] buffers)."""
+        """Restore the counters of a checkpoint (with columns [0, P) of the buffers)."""
         gasloc_set_counters(self.ctx, k, stepped, rounds_done)
 
     def set_alive(self, alive=None):

@@ -399,6 +399,15 @@ def test_noalloc_consensus_error_rejects_bad_output():
     assert "out must be" in g.gasloc.gasloc_last_error(None)
 
 
+def test_buffers_of_a_given_row_length():
+    """A program's own row length (that of a state it saved as whole buffers) is kept."""
+    pytest.importorskip("torch")
+    for dtype, own in (("f32", 4100), ("bf16", 4104)):
+        b = g.alloc_buffers(3, 4099, dtype, device="cpu", ld=own)
+        assert b["ld"] == own and all(b[k].shape == (3, own) for k in ("x", "y", "m", "v", "u", "zp"))
+        assert g.alloc_buffers(3, 4099, dtype, device="cpu")["ld"] == g.padded_ld(4099, dtype)
+
+
 def test_library_was_built_from_this_tree():
     # gasloc_build_info carries the hash of the sources the library was
     # compiled from; a library left over from other sources fails here

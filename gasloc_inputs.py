@@ -76,12 +76,6 @@ WORKLOAD_ORDER = ["ring-n4-p1m", "exp-n8-p124m", "onepeer-exp-n16-p350m",
                   "regular3-n32-p150m-bf16", "matching-n64-p50m-hetH"]
 
 
-def padded_ld(P, param_dtype):
-    """Row stride (elements) so that every row starts 16-byte aligned."""
-    per16 = 8 if param_dtype == "bf16" else 4
-    return (P + per16 - 1) // per16 * per16
-
-
 def local_steps(w: Workload):
     """Per-worker local-step counts H_i (fixed for the whole run)."""
     if w.hetero_H is None:

@@ -138,9 +138,13 @@ hipError_t launch_gossip_planned(const GossipArgs& a, int dtype, bool fused, int
                                  hipStream_t stream);
 // Rounds with the workers spread over the waves of a workgroup
 // (round_tile.hip): shape.threads / 64 waves with shape.batch workers each (1,
-// 2, 4 or 8), kTileVec columns per lane, a.tile_groups tiles per workgroup;
+// 2 or 4 to 8), kTileVec columns per lane, a.tile_groups tiles per workgroup;
 // `lds`: the bytes a.kept_off and a.sums_off were laid out in.
 constexpr int kTileVec = 4;
+// Bytes of one slot: the mixed values are parameters as stored except in the EQ form.
+constexpr size_t tile_slot_bytes(int dtype, int form) {
+  return dtype == GASLOC_BF16 && form != GASLOC_FORM_EQ ? 2 : 4;
+}
 hipError_t launch_gossip_tile(const GossipArgs& a, int dtype, bool fused, int form, const LaunchShape& shape,
                               size_t lds, hipStream_t stream);
 // Workgroups of the selected phase or planned round kernel that one CU

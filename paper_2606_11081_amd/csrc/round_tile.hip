@@ -3,8 +3,8 @@
 // workers w, w + W, w + 2W, ... (K of them at most, W waves), each lane V
 // consecutive columns of each.  The thread that loads a worker's streams also
 // finishes that worker's row, so every stream is read once, in one go, before
-// the first barrier, and what the row needs again (its own term, x, u) stays
-// in registers; only the mixed values (z for EQ, the live local iterate for
+// or around the first barrier, and what the row needs again (its own term, x, u)
+// stays in registers; only the mixed values (z for EQ, the live local iterate for
 // ALG1, x for the DAdam forms) cross waves, through LDS.  The stored rows go
 // through LDS too, so that one thread per column sums the consensus error of
 // all workers in worker order.  Per element the arithmetic is exactly that of
@@ -37,13 +37,66 @@ typedef const __attribute__((address_space(4))) float uniform_f32;
 
 constexpr int kWaitVector = 0x0f70;  // s_waitcnt vmcnt(0); the other counters are not waited for
 
-// What a worker's row needs after the barrier, by form: EQ the consensus
-// momentum term; ALG1 x and u; DAdam y - x; Local-DAdam x, y and u.
-template <int V, int FORM>
-struct RowKept {
-  static constexpr int count = FORM == GASLOC_FORM_ALG1 ? 2 : (FORM == GASLOC_FORM_LOCAL_DADAM ? 3 : 1);
-  float v[count][V];
+// V parameters as stored: fp32, or two bf16 values to a register.
+template <int DT, int V>
+struct Held {
+  uint32_t w[DT == GASLOC_BF16 ? V / 2 : V];
+  __device__ __forceinline__ void set(const float (&v)[V]) {
+#pragma unroll
+    for (int c = 0; c < V; ++c) {
+      const uint32_t bits = __float_as_uint(v[c]);
+      if constexpr (DT != GASLOC_BF16)
+        w[c] = bits;
+      else
+        w[c / 2] = c % 2 ? w[c / 2] | (bits & 0xffff0000u) : bits >> 16;
+    }
+  }
+  __device__ __forceinline__ float get(int c) const {
+    if constexpr (DT != GASLOC_BF16) return __uint_as_float(w[c]);
+    return __uint_as_float(c % 2 ? w[c / 2] & 0xffff0000u : w[c / 2] << 16);
+  }
 };
+
+// What a worker's row needs after the barrier and does not find in its slot, by
+// form: EQ the consensus momentum term; ALG1 x and u (the slot holds y); DAdam
+// y - x; Local-DAdam y and u (the slot holds x).
+template <int DT, int V, int FORM>
+struct RowKept {
+  static constexpr bool kOuter = FORM == GASLOC_FORM_ALG1 || FORM == GASLOC_FORM_LOCAL_DADAM;
+  Held<DT, kOuter ? V : 2> base;
+  float v[V];  // u, or the term
+};
+
+// The value of a slot, and a stored row's in LDS: 16 bits for what is a bf16
+// value already (stored rows; iterates and anchors, the mixed values of every
+// form but EQ), else fp32.
+template <int DT, int FORM>
+constexpr bool kSlot16 = DT == GASLOC_BF16 && FORM != GASLOC_FORM_EQ;
+
+// V values to and from LDS (HALF: as bf16).
+template <int V, bool HALF>
+__device__ __forceinline__ void lds_put(void* lds, int at, const Held<HALF ? GASLOC_BF16 : GASLOC_F32, V>& v) {
+  uint32_t* p = reinterpret_cast<uint32_t*>(static_cast<char*>(lds) + at * (HALF ? 2 : 4));
+#pragma unroll
+  for (int c = 0; c < (HALF ? V / 2 : V); ++c) p[c] = v.w[c];
+}
+
+template <int V, bool HALF>
+__device__ __forceinline__ void lds_get(const void* lds, int at, float (&v)[V]) {
+  Held<HALF ? GASLOC_BF16 : GASLOC_F32, V> h;
+  const uint32_t* p = reinterpret_cast<const uint32_t*>(static_cast<const char*>(lds) + at * (HALF ? 2 : 4));
+#pragma unroll
+  for (int c = 0; c < (HALF ? V / 2 : V); ++c) h.w[c] = p[c];
+#pragma unroll
+  for (int c = 0; c < V; ++c) v[c] = h.get(c);
+}
+
+// One value.
+template <bool HALF>
+__device__ __forceinline__ float lds_value(const void* lds, int at) {
+  if constexpr (HALF) return bf16_to_f32(static_cast<const uint16_t*>(lds)[at]);
+  return static_cast<const float*>(lds)[at];
+}
 
 // The streams of one worker as loaded (the forms other than EQ: y and u only
 // where the worker has them).
@@ -54,15 +107,16 @@ struct RowKept {
 // to 4% off: n=22, P=17.8M Local-DAdam 3.41 -> 3.31 ms, n=16, P=50M bf16
 // Algorithm 1 4.34 -> 4.23.  The EQ form, with more streams, is 1 to 3% faster
 // as it is (n=12, P=50M ring 5.74 against 5.93 ms, n=4, P=67M 2.08 against
-// 2.12, n=8, P=124M 7.87 against 7.98): more loads in flight than HBM needs
-// make its pages conflict.
+// 2.12, n=8, P=124M 7.87 against 7.98) except for waves of many workers
+// (kDeep in tile_round): more loads in flight than HBM needs make its pages
+// conflict.
 template <int V, bool FUSED, int FORM>
 struct WorkerLoads {
   float x[V], y[V], u[V], zp[V];
   float g[FUSED ? V : 1], m[FUSED ? V : 1], v[FUSED ? V : 1];
 };
 
-template <int DT, int V, bool FUSED, int FORM>
+template <int DT, int V, bool FUSED, int FORM, bool ONCE, bool LATE>
 __device__ __forceinline__ void tile_load(const GossipArgs& a, int i, int64_t tile0, int at, int cnt,
                                           WorkerLoads<V, FUSED, FORM>& w) {
   constexpr bool kEq = FORM == GASLOC_FORM_EQ;
@@ -71,7 +125,7 @@ __device__ __forceinline__ void tile_load(const GossipArgs& a, int i, int64_t ti
   load_params<DT, V>(static_cast<const char*>(a.x) + row * sp, at, cnt, w.x);
   if ((a.stepped >> i) & 1ull) {
     load_params<DT, V>(static_cast<const char*>(a.y) + row * sp, at, cnt, w.y);
-  } else if constexpr (kEq) {
+  } else if constexpr (!ONCE) {
 #pragma unroll
     for (int c = 0; c < V; ++c) w.y[c] = w.x[c];
   }
@@ -82,23 +136,23 @@ __device__ __forceinline__ void tile_load(const GossipArgs& a, int i, int64_t ti
       load_f32<V>(a.v + row + at, cnt, w.v);
     }
   }
-  if (FORM != GASLOC_FORM_DADAM && a.use_u) {
+  if (FORM != GASLOC_FORM_DADAM && !LATE && a.use_u) {
     load_f32<V>(a.u + row + at, cnt, w.u);
-  } else if constexpr (kEq) {
+  } else if constexpr (!ONCE) {
 #pragma unroll
     for (int c = 0; c < V; ++c) w.u[c] = 0.0f;
   }
   if (kEq && a.apply_gamma) load_f32<V>(a.zp + row + at, cnt, w.zp);
 }
 
-template <int DT, int V, bool FUSED, int FORM>
+template <int DT, int V, bool FUSED, int FORM, bool ONCE, bool LATE>
 __device__ __forceinline__ void tile_produce(const GossipArgs& a, int i, int64_t tile0, int at, int cnt,
-                                             WorkerLoads<V, FUSED, FORM>& w, float* slot, RowKept<V, FORM>& kept,
+                                             WorkerLoads<V, FUSED, FORM>& w, void* slots, RowKept<DT, V, FORM>& kept,
                                              double& pg) {
   const int64_t row = static_cast<int64_t>(i) * a.ld + tile0;  // uniform
-  if constexpr (FORM != GASLOC_FORM_EQ) {
+  if constexpr (ONCE) {
     const bool stepped = (a.stepped >> i) & 1ull;
-    const bool with_u = FORM != GASLOC_FORM_DADAM && a.use_u;
+    const bool with_u = FORM != GASLOC_FORM_DADAM && !LATE && a.use_u;
 #pragma unroll
     for (int c = 0; c < V; ++c) {
       w.y[c] = stepped ? w.y[c] : w.x[c];
@@ -112,7 +166,7 @@ __device__ __forceinline__ void tile_produce(const GossipArgs& a, int i, int64_t
       for (int c = 0; c < V; ++c)
         w.y[c] = as_stored<DT>(adamw_element(w.y[c], w.g[c], w.m[c], w.v[c], a.c_wd, a.b1, a.omb1, a.b2, a.omb2,
                                              a.eps, s1, c2));
-      if constexpr (FORM == GASLOC_FORM_EQ) {
+      if constexpr (!ONCE) {
         store_f32<V>(a.m + row + at, cnt, w.m);
         store_f32<V>(a.v + row + at, cnt, w.v);
       }
@@ -128,7 +182,7 @@ __device__ __forceinline__ void tile_produce(const GossipArgs& a, int i, int64_t
 #pragma unroll
     for (int c = 0; c < V; ++c) {
       out[c] = outer_step(w.x[c], w.x[c] - w.y[c], w.u[c], a.mu, a.eta, a.nesterov);
-      kept.v[0][c] = a.gamma * (out[c] - w.zp[c]);
+      kept.v[c] = a.gamma * (out[c] - w.zp[c]);
     }
     if (a.use_u) store_f32<V>(a.u + row + at, cnt, w.u);
     if (a.store_zp) store_f32<V>(a.zp + row + at, cnt, out);
@@ -136,29 +190,34 @@ __device__ __forceinline__ void tile_produce(const GossipArgs& a, int i, int64_t
 #pragma unroll
     for (int c = 0; c < V; ++c) {
       out[c] = FORM == GASLOC_FORM_ALG1 ? w.y[c] : w.x[c];
-      if constexpr (FORM == GASLOC_FORM_ALG1) {
-        kept.v[0][c] = w.x[c];
-        kept.v[1][c] = w.u[c];
-      } else if constexpr (FORM == GASLOC_FORM_DADAM) {
-        kept.v[0][c] = w.y[c] - w.x[c];
-      } else {
-        kept.v[0][c] = w.x[c];
-        kept.v[1][c] = w.u[c];
-        kept.v[2][c] = w.y[c];
-      }
+      if constexpr (FORM == GASLOC_FORM_DADAM)
+        kept.v[c] = w.y[c] - w.x[c];
+      else if constexpr (!LATE)
+        kept.v[c] = w.u[c];
     }
+    if constexpr (FORM == GASLOC_FORM_ALG1) kept.base.set(w.x);
+    if constexpr (FORM == GASLOC_FORM_LOCAL_DADAM) kept.base.set(w.y);
   }
-#pragma unroll
-  for (int c = 0; c < V; ++c) slot[c] = out[c];
+  Held<kSlot16<DT, FORM> ? GASLOC_BF16 : GASLOC_F32, V> held;
+  held.set(out);
+  lds_put<V, kSlot16<DT, FORM>>(slots, i * kWave * V + at, held);
 }
 
 // Row i from the slots: res, and u where the form updates it there.
-template <int V, int FORM>
+template <int DT, int V, int FORM>
 __device__ __forceinline__ void tile_row(const GossipArgs& a, uniform_i32* rp, uniform_i32* col, uniform_f32* val,
-                                         int i, const float* zs, const float* shared_sum, int at,
-                                         RowKept<V, FORM>& kept, float (&res)[V]) {
+                                         int i, const void* slots, const float* shared_sum, int at,
+                                         RowKept<DT, V, FORM>& kept, float (&res)[V]) {
   constexpr int C = kWave * V;
+  constexpr bool kHalf = kSlot16<DT, FORM>;
   constexpr bool kDiff = FORM == GASLOC_FORM_ALG1 || FORM == GASLOC_FORM_LOCAL_DADAM;
+  float own[V];  // x, which the forms on differences measure them from
+  if constexpr (FORM == GASLOC_FORM_LOCAL_DADAM) {
+    lds_get<V, kHalf>(slots, i * C + at, own);
+  } else if constexpr (FORM == GASLOC_FORM_ALG1) {
+#pragma unroll
+    for (int c = 0; c < V; ++c) own[c] = kept.base.get(c);
+  }
 #pragma unroll
   for (int c = 0; c < V; ++c) res[c] = 0.0f;
   if (!kDiff && shared_sum) {
@@ -171,52 +230,51 @@ __device__ __forceinline__ void tile_row(const GossipArgs& a, uniform_i32* rp, u
 #pragma unroll
       for (int t = 0; t < 4; ++t) {
         if (k0 + t >= ke) break;
-        const float* src = zs + col[k0 + t] * C + at;
+        lds_get<V, kHalf>(slots, col[k0 + t] * C + at, zk[t]);
         wk[t] = val[k0 + t];
-#pragma unroll
-        for (int c = 0; c < V; ++c) zk[t][c] = src[c];
       }
 #pragma unroll
       for (int t = 0; t < 4; ++t) {
         if (k0 + t >= ke) break;
 #pragma unroll
-        for (int c = 0; c < V; ++c) res[c] = res[c] + wk[t] * (kDiff ? kept.v[0][c] - zk[t][c] : zk[t][c]);
+        for (int c = 0; c < V; ++c) res[c] = res[c] + wk[t] * (kDiff ? own[c] - zk[t][c] : zk[t][c]);
       }
     }
   }
   if constexpr (FORM == GASLOC_FORM_EQ) {
     if (a.apply_gamma) {
 #pragma unroll
-      for (int c = 0; c < V; ++c) res[c] = res[c] + kept.v[0][c];
+      for (int c = 0; c < V; ++c) res[c] = res[c] + kept.v[c];
     }
   } else if constexpr (FORM == GASLOC_FORM_DADAM) {
 #pragma unroll
-    for (int c = 0; c < V; ++c) res[c] = res[c] + kept.v[0][c];
+    for (int c = 0; c < V; ++c) res[c] = res[c] + kept.v[c];
   } else {
 #pragma unroll
     for (int c = 0; c < V; ++c)
-      res[c] = outer_step(kept.v[FORM == GASLOC_FORM_ALG1 ? 0 : 2][c], res[c], kept.v[1][c], a.mu, a.eta, a.nesterov);
+      res[c] = outer_step(kept.base.get(c), res[c], kept.v[c], a.mu, a.eta, a.nesterov);
   }
 }
-
-// What a stored value is kept as in LDS for the consensus error.
-template <int DT>
-struct KeptWord {
-  typedef float type;
-};
-template <>
-struct KeptWord<GASLOC_BF16> {
-  typedef uint16_t type;
-};
 
 // One tile.  TAIL: the tile runs past P (cnt < V in some lanes).
 template <int DT, int V, int K, bool FUSED, int FORM, bool TAIL>
 __device__ __forceinline__ void tile_round(const GossipArgs& a, unsigned char* lds, int64_t tile0, double& ce,
                                            double& pg) {
-  typedef typename KeptWord<DT>::type kept_t;
   constexpr int C = kWave * V;
   constexpr int sp = DT == GASLOC_BF16 ? 2 : 4;
-  constexpr int B = K < 2 ? K : 2;  // workers whose loads are issued together (4: no faster; spills when fused)
+  constexpr int B = K < 2 ? K : 2;  // workers whose loads are issued together (4: up to 20% slower)
+  // A wave with many workers of few streams (the round alone) waits for memory
+  // more than it loads: there all loads of a batch go out at once with one wait
+  // in every form, and u, which only the rows need, is loaded for all of the
+  // wave's workers together after the values, in flight across the barrier.
+  // Local step, then round, n=40, P=6.7M bf16 2-Peer: EQ, gamma = 0, 2.02 -> 1.86
+  // ms; Algorithm 1 1.86 -> 1.76.  With four workers in fp32 neither helps (EQ,
+  // gamma = 0.1, n=17, P=15.8M 2.58 -> 2.68).  Eight workers and the fused step
+  // take u late for the registers' sake: u and x of all eight next to a
+  // batch's six streams do not fit 128.
+  constexpr bool kDeep = !FUSED && (K >= 5 || (K == 4 && DT == GASLOC_BF16));
+  constexpr bool kOnce = FORM != GASLOC_FORM_EQ || kDeep;
+  constexpr bool kLate = RowKept<DT, V, FORM>::kOuter && (kDeep || K == 8);
   const int n = a.n;
   const int lane = threadIdx.x % kWave;
   const int wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x) / kWave);
@@ -227,38 +285,53 @@ __device__ __forceinline__ void tile_round(const GossipArgs& a, unsigned char* l
     const int64_t left = a.P - tile0 - at;
     cnt = left >= V ? V : (left > 0 ? static_cast<int>(left) : 0);
   }
-  float* zs = reinterpret_cast<float*>(lds);
-  kept_t* xs = reinterpret_cast<kept_t*>(lds + a.kept_off);
+  constexpr bool kHalf = kSlot16<DT, FORM>;
+  constexpr bool kHalfRows = DT == GASLOC_BF16;
+  unsigned char* slots = lds;
+  unsigned char* xs = lds + a.kept_off;
   float* sums = reinterpret_cast<float*>(lds + a.sums_off);
   uniform_i32* rp = (uniform_i32*)(a.row_ptr);
   uniform_i32* col = (uniform_i32*)(a.col);
   uniform_f32* val = (uniform_f32*)(a.val);
 
-  RowKept<V, FORM> kept[K];
+  RowKept<DT, V, FORM> kept[K];
 #pragma unroll
   for (int k0 = 0; k0 < K; k0 += B) {
     WorkerLoads<V, FUSED, FORM> w[B];
 #pragma unroll
     for (int b = 0; b < B; ++b) {
       const int i = wave + (k0 + b) * waves;
-      if (i < n) tile_load<DT, V, FUSED, FORM>(a, i, tile0, at, cnt, w[b]);
+      if (k0 + b < K && i < n) tile_load<DT, V, FUSED, FORM, kOnce, kLate>(a, i, tile0, at, cnt, w[b]);
     }
     // One wait for the batch, after which no load is pending on any path
-    if constexpr (FORM != GASLOC_FORM_EQ) __builtin_amdgcn_s_waitcnt(kWaitVector);
+    if constexpr (kOnce) __builtin_amdgcn_s_waitcnt(kWaitVector);
 #pragma unroll
     for (int b = 0; b < B; ++b) {
       const int i = wave + (k0 + b) * waves;
-      if (i < n) tile_produce<DT, V, FUSED, FORM>(a, i, tile0, at, cnt, w[b], zs + i * C + at, kept[k0 + b], pg);
+      if (k0 + b < K && i < n) tile_produce<DT, V, FUSED, FORM, kOnce, kLate>(a, i, tile0, at, cnt, w[b], slots, kept[k0 + b], pg);
     }
-    if constexpr (FUSED && FORM != GASLOC_FORM_EQ) {  // the batch's moments, once all its values are computed
+    if constexpr (FUSED && kOnce) {  // the batch's moments, once all its values are computed
 #pragma unroll
       for (int b = 0; b < B; ++b) {
         const int i = wave + (k0 + b) * waves;
-        if (i < n && ((a.active >> i) & 1ull)) {
+        if (k0 + b < K && i < n && ((a.active >> i) & 1ull)) {
           const int64_t e = static_cast<int64_t>(i) * a.ld + tile0 + at;
           store_f32<V>(a.m + e, cnt, w[b].m);
           store_f32<V>(a.v + e, cnt, w[b].v);
         }
+      }
+    }
+  }
+  if constexpr (kLate) {
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+      const int i = wave + k * waves;
+      if (i >= n) break;
+      if (a.use_u) {
+        load_f32<V>(a.u + static_cast<int64_t>(i) * a.ld + tile0 + at, cnt, kept[k].v);
+      } else {
+#pragma unroll
+        for (int c = 0; c < V; ++c) kept[k].v[c] = 0.0f;
       }
     }
   }
@@ -268,34 +341,36 @@ __device__ __forceinline__ void tile_round(const GossipArgs& a, unsigned char* l
   if (shared) {
     for (int c = threadIdx.x; c < C; c += blockDim.x) {
       float s = 0.0f;
-      for (int k = 0; k < a.sum_entries; ++k) s = s + a.sum_w[k] * zs[a.sum_col[k] * C + c];
+      for (int k = 0; k < a.sum_entries; ++k) s = s + a.sum_w[k] * lds_value<kHalf>(slots, a.sum_col[k] * C + c);
       sums[c] = s;
     }
     __syncthreads();
   }
-  float res[K][V];
-#pragma unroll
-  for (int k = 0; k < K; ++k) {
-    const int i = wave + k * waves;
-    if (i < n) tile_row<V, FORM>(a, rp, col, val, i, zs, shared ? sums : nullptr, at, kept[k], res[k]);
-  }
-  if (a.kept_off == 0) __syncthreads();  // every slot has been read: the stored rows take their place
+  // Rows, each stored as soon as it is summed; in LDS, when they take the slots'
+  // place, once every slot has been read.
+  const bool in_place = a.kept_off == 0;
+  Held<DT, V> stored[K];
 #pragma unroll
   for (int k = 0; k < K; ++k) {
     const int i = wave + k * waves;
     if (i >= n) break;
     const int64_t row = static_cast<int64_t>(i) * a.ld + tile0;
-    float stored[V];
-    store_params<DT, V>(static_cast<char*>(a.x) + row * sp, at, cnt, res[k], stored);
+    float res[V], kept_x[V];
+    tile_row<DT, V, FORM>(a, rp, col, val, i, slots, shared ? sums : nullptr, at, kept[k], res);
+    store_params<DT, V>(static_cast<char*>(a.x) + row * sp, at, cnt, res, kept_x);
+    stored[k].set(kept_x);
     if constexpr (FORM == GASLOC_FORM_ALG1 || FORM == GASLOC_FORM_LOCAL_DADAM) {
-      if (a.use_u) store_f32<V>(a.u + row + at, cnt, kept[k].v[1]);
+      if (a.use_u) store_f32<V>(a.u + row + at, cnt, kept[k].v);
     }
+    if (!in_place) lds_put<V, kHalfRows>(xs, i * C + at, stored[k]);
+  }
+  if (in_place) {
+    __syncthreads();
 #pragma unroll
-    for (int c = 0; c < V; ++c) {
-      if constexpr (DT == GASLOC_BF16)
-        xs[i * C + at + c] = static_cast<uint16_t>(__float_as_uint(stored[c]) >> 16);
-      else
-        xs[i * C + at + c] = stored[c];
+    for (int k = 0; k < K; ++k) {
+      const int i = wave + k * waves;
+      if (i >= n) break;
+      lds_put<V, kHalfRows>(xs, i * C + at, stored[k]);
     }
   }
   __syncthreads();
@@ -303,12 +378,7 @@ __device__ __forceinline__ void tile_round(const GossipArgs& a, unsigned char* l
   const double inv_n = 1.0 / static_cast<double>(n);
   const int cols = TAIL ? static_cast<int>(a.P - tile0 < C ? a.P - tile0 : C) : C;
   for (int c = threadIdx.x; c < cols; c += blockDim.x) {
-    auto value = [&](int i) {
-      if constexpr (DT == GASLOC_BF16)
-        return static_cast<double>(bf16_to_f32(xs[i * C + c]));
-      else
-        return static_cast<double>(xs[i * C + c]);
-    };
+    auto value = [&](int i) { return static_cast<double>(lds_value<kHalfRows>(xs, i * C + c)); };
     const double shift = value(0);
     double s = 0.0, q = 0.0;
     for (int i = 1; i < n; ++i) {
@@ -350,6 +420,9 @@ hipError_t with_tile_workers(int per_wave, F& f) {
     case 1: return f(reinterpret_cast<const void*>(&k_gossip_tile<DT, kTileVec, 1, FUSED, FORM>));
     case 2: return f(reinterpret_cast<const void*>(&k_gossip_tile<DT, kTileVec, 2, FUSED, FORM>));
     case 4: return f(reinterpret_cast<const void*>(&k_gossip_tile<DT, kTileVec, 4, FUSED, FORM>));
+    case 5: return f(reinterpret_cast<const void*>(&k_gossip_tile<DT, kTileVec, 5, FUSED, FORM>));
+    case 6: return f(reinterpret_cast<const void*>(&k_gossip_tile<DT, kTileVec, 6, FUSED, FORM>));
+    case 7: return f(reinterpret_cast<const void*>(&k_gossip_tile<DT, kTileVec, 7, FUSED, FORM>));
     default: return f(reinterpret_cast<const void*>(&k_gossip_tile<DT, kTileVec, 8, FUSED, FORM>));
   }
 }

@@ -381,29 +381,56 @@ RoundKernel pick_round_kernel() {
 //
 // One tile per workgroup (several only if the partials buffer requires it): 2,
 // 4 and 8 tiles took 2, 5 and 8% longer (n=4, P=67M fp32, fused; the same on
-// n=2, 3, 6).  Workers per wave: with few tiles per CU the fewest that 16
-// waves allow, for the shortest chain in a wave; with many tiles twice that,
-// so that a workgroup has 8 waves or fewer and several of them, in different
-// phases, share a CU.  Fused step + round, the fewest against twice that (and
-// four times): n=16, P=65k fp32 15.8 against 14.1 (18.0) us, P=4.2M 638
-// against 655 (759) us, P=50M bf16 Algorithm 1 5.51 against 4.96 (4.87) ms;
-// n=32, P=2.1M 668 against 692 us, P=40M bf16 3-regular 9.03 against 8.78 ms;
-// n=64, P=1.05M 694 against 717 us, P=25M matching 10.17 against 9.49 ms.
-// The line is at 64 tiles per CU, between the sizes that prefer either.
+// n=2, 3, 6).
+//
+// Workers per wave, up to 32 workers: with few tiles per CU the fewest that 16
+// waves allow, for the shortest chain in a wave; with many tiles twice that, so
+// that a workgroup has 8 waves or fewer and several of them, in different
+// phases, share a CU.  Fused step + round, fp32, fewest / twice / four times
+// that: n=16, P=65536 14.3 / 14.4 / 17.2 us, P=1.05M 140 / 144 / 147 us,
+// P=16.8M 1.98 / 1.89 / 1.88 ms; n=32, P=65536 20.9 / 24.0 / 29.6 us, P=8.4M
+// complete 2.04 / 1.88 / 2.02 ms; n=8, P=1.05M 69 / 72 / 75 us, P=4.2M 261 /
+// 278 / 295, P=33.6M 1.87 / 1.90 / 1.90 ms.  The line at 64 tiles per CU lies
+// between the sizes at which 16 and 32 workers change sides; 8 workers lose up
+// to 6% past it, and with about 4 tiles per CU (P=262144) twice the fewest
+// would be 3 to 5% faster (n=16 36.9 against 38.3 us).
+//
+// Beyond 32 workers: 16 waves with less than two tiles per CU (n=64, P=65536
+// 42.9 us against 45.5 with 8 waves); from there 8 waves, two on each SIMD,
+// with as many workers as that takes, so that the registers hold two workgroups
+// or more per CU where 16 waves fill it with one.  Same buffers, 16 / 8 waves:
+// n=64, P=131072 80.8 / 74.9 us, P=500k 285 / 271, P=1M 586 / 559, P=700k 410 /
+// 424; n=40, P=400k 169 / 151, P=1M 367 / 343; n=56, P=1M 506 / 487; bf16,
+// local step, then round, n=40, P=6.7M Local-DAdam 1.85 / 1.77 ms, n=64, P=4.2M
+// 1.80 / 1.73.  Waves that do not spread evenly over the SIMDs cost more than
+// either: 5 waves of 8 workers at n=40, P=1M 372 us, and the Local-DAdam pass
+// 2.0 ms.  Two exceptions: the fused Algorithm 1 kernel, whose rows keep x and u
+// next to six streams, stays with 16 waves up to 48 workers (n=36, P=7.5M 1.85
+// against 2.04 ms, n=48 1.79 / 1.85; n=52 2.02 / 1.98); the EQ round alone in
+// bf16, whose 78 registers let two workgroups of 12 waves share a CU, takes 12
+// from 41 to 60 workers (step, then round, gamma = 0, n=56, P=4.8M 1.76 against
+// 1.86 ms, n=52 1.93 / 1.96; n=48, P=700k 270 us / 277).
 // The stored rows get LDS of their own up to 32 workers; beyond, they take the
 // slots' place after one more barrier, so that two workgroups fit a CU (n=64,
 // P=25M matching: 11.57 ms with LDS of their own, 9.42 ms in place).
-gasloc::LaunchShape pick_tile_shape(const gasloc_ctx& c, gasloc::GossipArgs* a, size_t* lds) {
+gasloc::LaunchShape pick_tile_shape(const gasloc_ctx& c, bool fused, gasloc::GossipArgs* a, size_t* lds) {
   constexpr int64_t kCols = 64 * gasloc::kTileVec;
   const int64_t tiles = (c.P + kCols - 1) / kCols;
   const int fewest = c.n <= 16 ? 1 : (c.n <= 32 ? 2 : 4);
-  int per_wave = tiles < 64 * static_cast<int64_t>(c.cus) ? fewest : 2 * fewest;
+  const int64_t cus = c.cus;
+  int per_wave = tiles < 64 * cus ? fewest : 2 * fewest;
+  if (c.n > 32) {
+    const bool narrow = c.hp.param_dtype == GASLOC_BF16 && c.hp.round_form == GASLOC_FORM_EQ && !fused;
+    const bool wide = c.hp.round_form == GASLOC_FORM_ALG1 && fused;
+    const int waves = tiles < 2 * cus || (wide && c.n <= 48) ? 16 : (narrow && c.n > 40 && c.n <= 60 ? 12 : 8);
+    per_wave = waves == 16 ? fewest : (c.n + waves - 1) / waves;
+  }
   bool in_place = c.n > 32;
   int64_t per = 1;
 #ifdef GASLOC_TUNING
   if (const char* env = std::getenv("GASLOC_TILE")) {
     int k = 0, p = 0, t = 0;
-    if (std::sscanf(env, "%d,%d,%d", &k, &p, &t) == 3 && (k == 1 || k == 2 || k == 4 || k == 8) && t >= 1) {
+    if (std::sscanf(env, "%d,%d,%d", &k, &p, &t) == 3 && k >= 1 && k <= 8 && t >= 1) {
       per_wave = 16 * k >= c.n ? k : 4;
       in_place = p != 0;
       per = t;
@@ -412,7 +439,7 @@ gasloc::LaunchShape pick_tile_shape(const gasloc_ctx& c, gasloc::GossipArgs* a, 
 #endif
   per = std::max<int64_t>(per, (tiles + gasloc::kMaxPartials - 1) / gasloc::kMaxPartials);
   const size_t slots = static_cast<size_t>(c.n) * kCols;
-  size_t end = slots * sizeof(float);
+  size_t end = slots * gasloc::tile_slot_bytes(c.hp.param_dtype, c.hp.round_form);
   a->kept_off = 0;
   if (!in_place) {
     a->kept_off = static_cast<int32_t>(end);
@@ -560,7 +587,7 @@ gasloc_status run_round(gasloc_ctx* c, const gasloc_csr* W, uint64_t t, const St
       std::memcpy(a.sum_col, col, sizeof(int32_t) * static_cast<size_t>(rp[1]));
       std::memcpy(a.sum_w, val, sizeof(float) * static_cast<size_t>(rp[1]));
     }
-    shape = pick_tile_shape(*c, &a, &lds);
+    shape = pick_tile_shape(*c, step != nullptr, &a, &lds);
     lds += gasloc::kStaticLds;
   } else if (planned) {
     // 4 columns per thread when the plan needs few slots (n=64 1-Peer: 10.7-

@@ -43,3 +43,24 @@ def test_host_objects_embed_the_device_binaries():
             obj = os.path.join(lib_build.BUILD, os.path.splitext(src)[0] + ".o")
             data = open(obj, "rb").read()
             assert b"__CLANG_OFFLOAD_BUNDLE__" in data, src
+
+
+READELF = os.path.join(ROCM, "llvm", "bin", "llvm-readelf")
+
+
+@pytest.mark.skipif(not (os.path.exists(BUNDLER) and os.path.exists(READELF)), reason="ROCm LLVM tools absent")
+@pytest.mark.parametrize("src", [s for s in lib_build.SOURCES if s.endswith(".hip")])
+def test_no_kernel_spills(src, tmp_path):
+    """Every kernel's working set stays in its registers: no scratch memory, no spilled vector register."""
+    fatbin = lib_build.device_binary(src)
+    if not os.path.exists(fatbin):
+        pytest.skip("library not built")
+    co = str(tmp_path / "kernels.co")
+    subprocess.run([BUNDLER, "--unbundle", "--type=o", "--targets=hipv4-amdgcn-amd-amdhsa--gfx950",
+                    "--input=" + fatbin, "--output=" + co], check=True, capture_output=True)
+    notes = subprocess.run([READELF, "--notes", co], check=True, capture_output=True, text=True).stdout
+    names = re.findall(r"\.name: +(_Z\S+)", notes)
+    scratch = [int(v) for v in re.findall(r"\.private_segment_fixed_size: (\d+)", notes)]
+    spills = [int(v) for v in re.findall(r"\.vgpr_spill_count: (\d+)", notes)]
+    assert names and len(names) == len(scratch) == len(spills)
+    assert not [k for k in zip(names, scratch, spills) if k[1] or k[2]]

@@ -36,7 +36,7 @@ LARGE = [
 ]
 
 
-def _rounds(kernel, n, P, graph, form, dtype, gamma, fused, rounds=2):
+def _rounds(kernel, n, P, graph, form, dtype, gamma, fused, rounds=2, mu=gi.OUTER_MOMENTUM):
     import torch
 
     import paper_2606_11081_amd as g
@@ -46,7 +46,7 @@ def _rounds(kernel, n, P, graph, form, dtype, gamma, fused, rounds=2):
         if kernel:
             os.environ["GASLOC_GOSSIP_KERNEL"] = kernel
         run = g.GASLoC(n, P, topology=graph, seed=5, degree=4, param_dtype=dtype, outer_lr=gi.OUTER_LR,
-                       outer_momentum=gi.OUTER_MOMENTUM, consensus_momentum=gamma, round_form=form)
+                       outer_momentum=mu, consensus_momentum=gamma, round_form=form)
         gen = torch.Generator(device="cuda")
         gen.manual_seed(n + P)
         run.x.normal_(0.0, 0.02, generator=gen)
@@ -69,11 +69,11 @@ def _rounds(kernel, n, P, graph, form, dtype, gamma, fused, rounds=2):
             os.environ["GASLOC_GOSSIP_KERNEL"] = before
 
 
-def _compare(n, P, *case):
+def _compare(n, P, *case, **options):
     import torch
 
-    a, sa = _rounds(None, n, P, *case)
-    b, sb = _rounds("planned", n, P, *case)
+    a, sa = _rounds(None, n, P, *case, **options)
+    b, sb = _rounds("planned", n, P, *case, **options)
     for k in a:
         view = torch.int16 if a[k].dtype == torch.bfloat16 else torch.int32
         assert torch.equal(a[k].contiguous().view(view), b[k].contiguous().view(view)), k
@@ -91,3 +91,41 @@ def test_tile_edges(n, P, graph, form, dtype, gamma, fused):
 def test_tile_workers_per_wave(n, graph, form, dtype, gamma, fused):
     print("case tile workers per wave n=%d %s %s %s" % (n, graph, form, dtype), flush=True)
     _compare(n, MANY_TILES, graph, form, dtype, gamma, fused)
+
+
+TWO_PER_CU = 2 * 256 * 256 + 3  # past the line at two tiles per CU (beyond 32 workers), with a ragged last tile
+BEYOND_32 = [  # 8 waves with 5, 6, 7 and 8 workers each, whole and not
+    (33, "two_peer", "local_dadam", "bf16", 0.0, False),
+    (40, "exponential", "alg1", "bf16", 0.0, True),
+    (41, "complete", "eq", "bf16", 0.0, False),
+    (48, "one_peer", "alg1", "f32", 0.0, False),
+    (49, "two_peer", "eq", "f32", 0.1, True),
+    (56, "ring", "dadam", "bf16", 0.0, False),
+    (57, "two_peer", "alg1", "f32", 0.0, True),
+    (63, "exponential", "local_dadam", "f32", 0.0, False),
+    (64, "complete", "dadam", "bf16", 0.0, False),
+    (64, "two_peer", "eq", "bf16", 0.1, False),
+]
+
+
+@pytest.mark.parametrize("n,graph,form,dtype,gamma,fused", BEYOND_32)
+def test_tile_eight_waves(n, graph, form, dtype, gamma, fused):
+    print("case tile eight waves n=%d %s %s %s" % (n, graph, form, dtype), flush=True)
+    _compare(n, TWO_PER_CU, graph, form, dtype, gamma, fused)
+
+
+@pytest.mark.parametrize("n,form,dtype,fused", [(20, "alg1", "bf16", False), (32, "local_dadam", "bf16", False),
+                                                (31, "eq", "bf16", False), (26, "alg1", "f32", True)])
+def test_tile_four_workers_per_wave(n, form, dtype, fused):
+    """The batches of four workers per wave that go out at once, and those that do not."""
+    print("case tile four workers per wave n=%d %s %s" % (n, form, dtype), flush=True)
+    _compare(n, MANY_TILES, "two_peer", form, dtype, 0.0, fused)
+
+
+@pytest.mark.parametrize("mu", [0.0, 0.9])
+@pytest.mark.parametrize("n,P", [(40, TWO_PER_CU), (64, TWO_PER_CU), (28, MANY_TILES)])
+@pytest.mark.parametrize("form,dtype", [("alg1", "bf16"), ("local_dadam", "f32"), ("eq", "bf16")])
+def test_tile_with_and_without_outer_momentum(form, dtype, n, P, mu):
+    """u present and absent: it is loaded with the values or with the rows, by form and workers per wave."""
+    print("case tile momentum n=%d %s %s mu=%g" % (n, form, dtype, mu), flush=True)
+    _compare(n, P, "two_peer", form, dtype, 0.0, False, mu=mu)

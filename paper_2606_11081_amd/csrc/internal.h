@@ -137,8 +137,8 @@ hipError_t launch_gossip_round(const GossipArgs& a, int dtype, bool fused, int f
 hipError_t launch_gossip_planned(const GossipArgs& a, int dtype, bool fused, int form, const LaunchShape& shape,
                                  hipStream_t stream);
 // Rounds with the workers spread over the waves of a workgroup
-// (round_tile.hip): shape.threads / 64 waves with shape.batch workers each (1,
-// 2 or 4 to 8), kTileVec columns per lane, a.tile_groups tiles per workgroup;
+// (round_tile.hip): shape.threads / 64 waves with shape.batch workers each (1
+// to 8; 3 in the fused EQ kernel only), kTileVec columns per lane, a.tile_groups tiles per workgroup;
 // `lds`: the bytes a.kept_off and a.sums_off were laid out in.
 constexpr int kTileVec = 4;
 // Bytes of one slot: the mixed values are parameters as stored except in the EQ form.

@@ -419,6 +419,10 @@ hipError_t with_tile_workers(int per_wave, F& f) {
   switch (per_wave) {
     case 1: return f(reinterpret_cast<const void*>(&k_gossip_tile<DT, kTileVec, 1, FUSED, FORM>));
     case 2: return f(reinterpret_cast<const void*>(&k_gossip_tile<DT, kTileVec, 2, FUSED, FORM>));
+    case 3:
+      if constexpr (FUSED && FORM == GASLOC_FORM_EQ)
+        return f(reinterpret_cast<const void*>(&k_gossip_tile<DT, kTileVec, 3, FUSED, FORM>));
+      return hipErrorInvalidValue;
     case 4: return f(reinterpret_cast<const void*>(&k_gossip_tile<DT, kTileVec, 4, FUSED, FORM>));
     case 5: return f(reinterpret_cast<const void*>(&k_gossip_tile<DT, kTileVec, 5, FUSED, FORM>));
     case 6: return f(reinterpret_cast<const void*>(&k_gossip_tile<DT, kTileVec, 6, FUSED, FORM>));

@@ -393,7 +393,11 @@ RoundKernel pick_round_kernel() {
 // 278 / 295, P=33.6M 1.87 / 1.90 / 1.90 ms.  The line at 64 tiles per CU lies
 // between the sizes at which 16 and 32 workers change sides; 8 workers lose up
 // to 6% past it, and with about 4 tiles per CU (P=262144) twice the fewest
-// would be 3 to 5% faster (n=16 36.9 against 38.3 us).
+// would be 3 to 5% faster (n=16 36.9 against 38.3 us).  Where that makes five
+// waves, which do not spread evenly over four SIMDs, the fused EQ kernel (four
+// waves of it fit a SIMD) takes three workers per wave: n=9, P=29.8M 2.32 ->
+// 2.20 ms, bf16 2.20 -> 2.03; n=18, P=14.9M 2.35 -> 2.22, bf16 2.22 -> 2.06.
+// (Fused Algorithm 1 there: 1.72 with five waves, 1.84 with three.)
 //
 // Beyond 32 workers: 16 waves with less than two tiles per CU (n=64, P=65536
 // 42.9 us against 45.5 with 8 waves); from there 8 waves, two on each SIMD,
@@ -419,6 +423,8 @@ gasloc::LaunchShape pick_tile_shape(const gasloc_ctx& c, bool fused, gasloc::Gos
   const int fewest = c.n <= 16 ? 1 : (c.n <= 32 ? 2 : 4);
   const int64_t cus = c.cus;
   int per_wave = tiles < 64 * cus ? fewest : 2 * fewest;
+  const bool five = per_wave > fewest && (c.n + per_wave - 1) / per_wave == 5;
+  if (five && c.n <= 32 && fused && c.hp.round_form == GASLOC_FORM_EQ) per_wave = 3;
   if (c.n > 32) {
     const bool narrow = c.hp.param_dtype == GASLOC_BF16 && c.hp.round_form == GASLOC_FORM_EQ && !fused;
     const bool wide = c.hp.round_form == GASLOC_FORM_ALG1 && fused;

@@ -122,6 +122,12 @@ def test_tile_four_workers_per_wave(n, form, dtype, fused):
     _compare(n, MANY_TILES, "two_peer", form, dtype, 0.0, fused)
 
 
+@pytest.mark.parametrize("n,dtype", [(9, "f32"), (10, "bf16"), (17, "bf16"), (20, "f32")])
+def test_tile_three_workers_per_wave(n, dtype):
+    print("case tile three workers per wave n=%d %s" % (n, dtype), flush=True)
+    _compare(n, MANY_TILES, "two_peer", "eq", dtype, 0.1, True)
+
+
 @pytest.mark.parametrize("mu", [0.0, 0.9])
 @pytest.mark.parametrize("n,P", [(40, TWO_PER_CU), (64, TWO_PER_CU), (28, MANY_TILES)])
 @pytest.mark.parametrize("form,dtype", [("alg1", "bf16"), ("local_dadam", "f32"), ("eq", "bf16")])

@@ -131,7 +131,7 @@ struct LaunchShape {
 };
 
 // Launchers: enqueue on `stream`, return the launch status.
-hipError_t launch_local_adamw(const AdamArgs& a, int dtype, hipStream_t stream);
+hipError_t launch_local_adamw(const AdamArgs& a, int dtype, int cus, hipStream_t stream);
 hipError_t launch_gossip_round(const GossipArgs& a, int dtype, bool fused, int form,
                                const LaunchShape& shape, hipStream_t stream);
 hipError_t launch_gossip_planned(const GossipArgs& a, int dtype, bool fused, int form, const LaunchShape& shape,

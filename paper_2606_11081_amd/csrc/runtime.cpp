@@ -860,7 +860,7 @@ gasloc_status gasloc_local_step(gasloc_ctx* c, const float* grads, int64_t grad_
     ++slots;
   }
   a.n_active = slots;
-  HIP_TRY(c, gasloc::launch_local_adamw(a, c->hp.param_dtype, c->stream));
+  HIP_TRY(c, gasloc::launch_local_adamw(a, c->hp.param_dtype, c->cus, c->stream));
   commit_step(c, plan);
   return GASLOC_OK;
 }

@@ -98,7 +98,7 @@ struct GossipArgs {
   int32_t slots;
 
   // k_gossip_tile only: byte offsets in LDS of the stored rows (0: they take
-  // the slots' place) and of the shared neighbour sums; if every row holds the
+  // the slots' place, from kInPlaceWorkers per wave) and of the shared neighbour sums; if every row holds the
   // entries of row 0 and the form sums them the same way, those entries (else
   // sum_entries is 0 and the rows are read from the CSR).  As arguments they
   // belong to the launch: one recorded in a graph keeps them, whatever the
@@ -141,6 +141,7 @@ hipError_t launch_gossip_planned(const GossipArgs& a, int dtype, bool fused, int
 // to 8; 3 in the fused EQ kernel only), kTileVec columns per lane, a.tile_groups tiles per workgroup;
 // `lds`: the bytes a.kept_off and a.sums_off were laid out in.
 constexpr int kTileVec = 4;
+constexpr int kInPlaceWorkers = 4;  // the fewest per wave that may store rows in the slots' place
 // Bytes of one slot: the mixed values are parameters as stored except in the EQ form.
 constexpr size_t tile_slot_bytes(int dtype, int form) {
   return dtype == GASLOC_BF16 && form != GASLOC_FORM_EQ ? 2 : 4;

@@ -57,13 +57,20 @@ struct Held {
   }
 };
 
-// What a worker's row needs after the barrier and does not find in its slot, by
-// form: EQ the consensus momentum term; ALG1 x and u (the slot holds y); DAdam
-// y - x; Local-DAdam y and u (the slot holds x).
-template <int DT, int V, int FORM>
+// The forms whose rows are outer steps from differences: they need u.
+template <int FORM>
+constexpr bool kOuterRow = FORM == GASLOC_FORM_ALG1 || FORM == GASLOC_FORM_LOCAL_DADAM;
+
+// What a worker's row needs after the barrier, by form: EQ the consensus
+// momentum term; ALG1 x and u; DAdam y - x; Local-DAdam x, y and u, where x is
+// what its slot holds: LEAN takes it from there (two registers or four per
+// worker saved; where they are not short the LDS read costs: n=11, P=1M local
+// step + round 99.5 us, 97.3 with x kept).
+template <int DT, int V, int FORM, bool LEAN>
 struct RowKept {
-  static constexpr bool kOuter = FORM == GASLOC_FORM_ALG1 || FORM == GASLOC_FORM_LOCAL_DADAM;
-  Held<DT, kOuter ? V : 2> base;
+  static constexpr bool kKeepsX = FORM == GASLOC_FORM_LOCAL_DADAM && !LEAN;
+  Held<DT, kOuterRow<FORM> ? V : 2> base;
+  Held<DT, kKeepsX ? V : 2> x;
   float v[V];  // u, or the term
 };
 
@@ -145,9 +152,9 @@ __device__ __forceinline__ void tile_load(const GossipArgs& a, int i, int64_t ti
   if (kEq && a.apply_gamma) load_f32<V>(a.zp + row + at, cnt, w.zp);
 }
 
-template <int DT, int V, bool FUSED, int FORM, bool ONCE, bool LATE>
+template <int DT, int V, bool FUSED, int FORM, bool ONCE, bool LATE, bool LEAN>
 __device__ __forceinline__ void tile_produce(const GossipArgs& a, int i, int64_t tile0, int at, int cnt,
-                                             WorkerLoads<V, FUSED, FORM>& w, void* slots, RowKept<DT, V, FORM>& kept,
+                                             WorkerLoads<V, FUSED, FORM>& w, void* slots, RowKept<DT, V, FORM, LEAN>& kept,
                                              double& pg) {
   const int64_t row = static_cast<int64_t>(i) * a.ld + tile0;  // uniform
   if constexpr (ONCE) {
@@ -197,6 +204,7 @@ __device__ __forceinline__ void tile_produce(const GossipArgs& a, int i, int64_t
     }
     if constexpr (FORM == GASLOC_FORM_ALG1) kept.base.set(w.x);
     if constexpr (FORM == GASLOC_FORM_LOCAL_DADAM) kept.base.set(w.y);
+    if constexpr (RowKept<DT, V, FORM, LEAN>::kKeepsX) kept.x.set(w.x);
   }
   Held<kSlot16<DT, FORM> ? GASLOC_BF16 : GASLOC_F32, V> held;
   held.set(out);
@@ -204,15 +212,18 @@ __device__ __forceinline__ void tile_produce(const GossipArgs& a, int i, int64_t
 }
 
 // Row i from the slots: res, and u where the form updates it there.
-template <int DT, int V, int FORM>
+template <int DT, int V, int FORM, bool LEAN>
 __device__ __forceinline__ void tile_row(const GossipArgs& a, uniform_i32* rp, uniform_i32* col, uniform_f32* val,
                                          int i, const void* slots, const float* shared_sum, int at,
-                                         RowKept<DT, V, FORM>& kept, float (&res)[V]) {
+                                         RowKept<DT, V, FORM, LEAN>& kept, float (&res)[V]) {
   constexpr int C = kWave * V;
   constexpr bool kHalf = kSlot16<DT, FORM>;
-  constexpr bool kDiff = FORM == GASLOC_FORM_ALG1 || FORM == GASLOC_FORM_LOCAL_DADAM;
+  constexpr bool kDiff = kOuterRow<FORM>;
   float own[V];  // x, which the forms on differences measure them from
-  if constexpr (FORM == GASLOC_FORM_LOCAL_DADAM) {
+  if constexpr (RowKept<DT, V, FORM, LEAN>::kKeepsX) {
+#pragma unroll
+    for (int c = 0; c < V; ++c) own[c] = kept.x.get(c);
+  } else if constexpr (FORM == GASLOC_FORM_LOCAL_DADAM) {
     lds_get<V, kHalf>(slots, i * C + at, own);
   } else if constexpr (FORM == GASLOC_FORM_ALG1) {
 #pragma unroll
@@ -274,7 +285,7 @@ __device__ __forceinline__ void tile_round(const GossipArgs& a, unsigned char* l
   // batch's six streams do not fit 128.
   constexpr bool kDeep = !FUSED && (K >= 5 || (K == 4 && DT == GASLOC_BF16));
   constexpr bool kOnce = FORM != GASLOC_FORM_EQ || kDeep;
-  constexpr bool kLate = RowKept<DT, V, FORM>::kOuter && (kDeep || K == 8);
+  constexpr bool kLate = kOuterRow<FORM> && (kDeep || K == 8);
   const int n = a.n;
   const int lane = threadIdx.x % kWave;
   const int wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x) / kWave);
@@ -294,7 +305,7 @@ __device__ __forceinline__ void tile_round(const GossipArgs& a, unsigned char* l
   uniform_i32* col = (uniform_i32*)(a.col);
   uniform_f32* val = (uniform_f32*)(a.val);
 
-  RowKept<DT, V, FORM> kept[K];
+  RowKept<DT, V, FORM, kDeep> kept[K];
 #pragma unroll
   for (int k0 = 0; k0 < K; k0 += B) {
     WorkerLoads<V, FUSED, FORM> w[B];
@@ -308,7 +319,8 @@ __device__ __forceinline__ void tile_round(const GossipArgs& a, unsigned char* l
 #pragma unroll
     for (int b = 0; b < B; ++b) {
       const int i = wave + (k0 + b) * waves;
-      if (k0 + b < K && i < n) tile_produce<DT, V, FUSED, FORM, kOnce, kLate>(a, i, tile0, at, cnt, w[b], slots, kept[k0 + b], pg);
+      if (k0 + b < K && i < n) tile_produce<DT, V, FUSED, FORM, kOnce, kLate, kDeep>(a, i, tile0, at, cnt, w[b], slots, kept[k0 + b],
+                                                               pg);
     }
     if constexpr (FUSED && kOnce) {  // the batch's moments, once all its values are computed
 #pragma unroll
@@ -348,7 +360,7 @@ __device__ __forceinline__ void tile_round(const GossipArgs& a, unsigned char* l
   }
   // Rows, each stored as soon as it is summed; in LDS, when they take the slots'
   // place, once every slot has been read.
-  const bool in_place = a.kept_off == 0;
+  const bool in_place = K >= kInPlaceWorkers && a.kept_off == 0;
   Held<DT, V> stored[K];
 #pragma unroll
   for (int k = 0; k < K; ++k) {
@@ -356,10 +368,10 @@ __device__ __forceinline__ void tile_round(const GossipArgs& a, unsigned char* l
     if (i >= n) break;
     const int64_t row = static_cast<int64_t>(i) * a.ld + tile0;
     float res[V], kept_x[V];
-    tile_row<DT, V, FORM>(a, rp, col, val, i, slots, shared ? sums : nullptr, at, kept[k], res);
+    tile_row<DT, V, FORM, kDeep>(a, rp, col, val, i, slots, shared ? sums : nullptr, at, kept[k], res);
     store_params<DT, V>(static_cast<char*>(a.x) + row * sp, at, cnt, res, kept_x);
     stored[k].set(kept_x);
-    if constexpr (FORM == GASLOC_FORM_ALG1 || FORM == GASLOC_FORM_LOCAL_DADAM) {
+    if constexpr (kOuterRow<FORM>) {
       if (a.use_u) store_f32<V>(a.u + row + at, cnt, kept[k].v);
     }
     if (!in_place) lds_put<V, kHalfRows>(xs, i * C + at, stored[k]);
@@ -399,7 +411,7 @@ __global__ __launch_bounds__(1024) void k_gossip_tile(GossipArgs a) {
   const int64_t t1 = tiles - t0 < a.tile_groups ? tiles : t0 + a.tile_groups;
   double ce = 0.0, pg = 0.0;
   for (int64_t t = t0; t < t1; ++t) {
-    if (a.kept_off == 0 && t > t0) __syncthreads();  // the stored rows of the tile before have been summed
+    if (K >= kInPlaceWorkers && a.kept_off == 0 && t > t0) __syncthreads();  // the stored rows of the tile before have been summed
     const int64_t tile0 = t * C;
     if (tile0 + C <= a.P)
       tile_round<DT, V, K, FUSED, FORM, false>(a, lds, tile0, ce, pg);

@@ -438,7 +438,7 @@ gasloc::LaunchShape pick_tile_shape(const gasloc_ctx& c, bool fused, gasloc::Gos
     int k = 0, p = 0, t = 0;
     if (std::sscanf(env, "%d,%d,%d", &k, &p, &t) == 3 && k >= 1 && k <= 8 && t >= 1) {
       per_wave = 16 * k >= c.n ? k : 4;
-      in_place = p != 0;
+      in_place = p != 0 && per_wave >= gasloc::kInPlaceWorkers;
       per = t;
     }
   }

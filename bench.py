@@ -49,22 +49,18 @@ CSRC = os.path.join(ROOT, "paper_2606_11081_amd", "csrc")
 # counter summary stays valid while its family's sources are unchanged
 KERNEL_FAMILIES = {
     "adamw": ("device_common.h", "internal.h", "adamw.hip", "runtime.cpp"),
-    "phase": ("device_common.h", "internal.h", "round_tile.hip", "round_phase.hip", "reductions.hip", "runtime.cpp"),
-    "planned": ("device_common.h", "internal.h", "round_tile.hip", "round_planned.hip", "reductions.hip", "runtime.cpp",
-                "plan.cpp"),
+    "tile": ("device_common.h", "internal.h", "round_tile.hip", "reductions.hip", "runtime.cpp"),
+    "planned": ("device_common.h", "internal.h", "round_planned.hip", "reductions.hip", "runtime.cpp", "plan.cpp"),
 }
 
 
 def kernel_family(kernel, n):
-    """Family of the kernel behind a profiled role: AdamW, or the gossip
-    kernels that may run the round (the tile kernel, in both families, unless
-    GASLOC_GOSSIP_KERNEL forces another)."""
+    """Family of the kernel behind a profiled role: AdamW, or the round kernel
+    that runs (the tile kernel for every n, unless GASLOC_GOSSIP_KERNEL asks
+    for the planned one)."""
     if kernel == "k_local_adamw":
         return "adamw"
-    forced = os.environ.get("GASLOC_GOSSIP_KERNEL", "")
-    if forced in ("phase", "planned"):
-        return forced
-    return "planned" if n > 16 else "phase"
+    return "planned" if os.environ.get("GASLOC_GOSSIP_KERNEL", "") == "planned" else "tile"
 
 
 def kernels_sha(family):

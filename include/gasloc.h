@@ -27,9 +27,9 @@
  *   - A context is not thread-safe; distinct contexts are independent.
  *   - After a device error every call on the context returns GASLOC_ESTATE.
  *   - The library reads one environment variable, a test hook:
- *     GASLOC_GOSSIP_KERNEL=phase|planned runs the rounds with one of two
- *     independent implementations in place of the tile kernel that runs them
- *     by default; stored results are bit-identical either way.
+ *     GASLOC_GOSSIP_KERNEL=planned runs the rounds with an independent
+ *     implementation in place of the tile kernel that runs them by default;
+ *     stored results are bit-identical either way.
  */
 #ifndef GASLOC_H
 #define GASLOC_H

@@ -18,7 +18,7 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 BUILD = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libgasloc.so")
-SOURCES = ["adamw.hip", "round_phase.hip", "round_planned.hip", "round_tile.hip", "reductions.hip",
+SOURCES = ["adamw.hip", "round_planned.hip", "round_tile.hip", "reductions.hip",
            "stream_probe.hip", "runtime.cpp", "topology.cpp", "schedule.cpp", "plan.cpp"]
 ARCH = "gfx950"
 

@@ -1,7 +1,6 @@
 // Internal interfaces between the C ABI (runtime.cpp), the schedule
 // generator (topology.cpp), the visit planner (plan.cpp) and the HIP kernels
-// (adamw.hip, round_tile.hip, round_phase.hip, round_planned.hip,
-// reductions.hip, with the
+// (adamw.hip, round_tile.hip, round_planned.hip, reductions.hip, with the
 // device helpers of device_common.h).  Not installed.
 #pragma once
 
@@ -85,7 +84,7 @@ struct GossipArgs {
   double* pg_partials;
   int64_t ld, P;
   int64_t tile_groups;
-  int32_t n, nnz;
+  int32_t n;
   float mu, eta, gamma;
   int32_t nesterov;
   int32_t use_u;        // outer momentum buffer present (mu != 0)
@@ -132,8 +131,6 @@ struct LaunchShape {
 
 // Launchers: enqueue on `stream`, return the launch status.
 hipError_t launch_local_adamw(const AdamArgs& a, int dtype, int cus, hipStream_t stream);
-hipError_t launch_gossip_round(const GossipArgs& a, int dtype, bool fused, int form,
-                               const LaunchShape& shape, hipStream_t stream);
 hipError_t launch_gossip_planned(const GossipArgs& a, int dtype, bool fused, int form, const LaunchShape& shape,
                                  hipStream_t stream);
 // Rounds with the workers spread over the waves of a workgroup
@@ -148,10 +145,8 @@ constexpr size_t tile_slot_bytes(int dtype, int form) {
 }
 hipError_t launch_gossip_tile(const GossipArgs& a, int dtype, bool fused, int form, const LaunchShape& shape,
                               size_t lds, hipStream_t stream);
-// Workgroups of the selected phase or planned round kernel that one CU
-// holds at once, given its registers, LDS and wave limits (0 if the query
-// fails).
-int phase_blocks_per_cu(int dtype, bool fused, int form, const LaunchShape& shape, size_t dyn_lds);
+// Workgroups of the selected planned round kernel that one CU holds at once,
+// given its registers, LDS and wave limits (0 if the query fails).
 int planned_blocks_per_cu(int dtype, bool fused, int form, const LaunchShape& shape, size_t dyn_lds);
 // Dynamic LDS bytes of one workgroup of the planned kernel (z slots only).
 size_t planned_lds_bytes(int slots, const LaunchShape& shape);
@@ -185,9 +180,7 @@ hipError_t launch_zero_rows(float* x, int64_t ld, int n, int64_t P, hipStream_t 
 hipError_t launch_replica_mean(const void* x, int dtype, int64_t ld, int n, int64_t P, void* out,
                                hipStream_t stream);
 
-// Dynamic LDS bytes one workgroup of the gossip kernel needs (z slots of
-// every thread plus the staged CSR); the kernel also uses kStaticLds bytes.
-size_t gossip_lds_bytes(int n, int nnz, const LaunchShape& shape);
+// LDS bytes of a round kernel's own reduction, beside its dynamic LDS.
 constexpr size_t kStaticLds = 2 * 1024 / 64 * sizeof(double);
 
 }  // namespace gasloc

@@ -9,7 +9,7 @@
 // grouped into super-steps: the z of up to kPlanBatch workers are computed
 // together (their loads in flight at once), then up to kPlanRows rows are
 // emitted.  The per-row arithmetic, including the ascending-column summation
-// order of every row, is that of the phase kernel; only independent work is
+// order of every row, is that of the tile kernel; only independent work is
 // reordered.
 //
 // Rows with the same CSR entries (columns and weight bits) have bit-identical

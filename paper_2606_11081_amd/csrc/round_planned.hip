@@ -4,7 +4,8 @@
 // of them) into free LDS slots, then emits up to kPlanRows rows.  LDS holds
 // `slots` values per column instead of n, so sparse graphs keep many more
 // columns in flight per CU.  Per element the arithmetic is exactly that of
-// k_gossip_round<..., FORM>.
+// k_gossip_tile<..., FORM>, of which this is the independent second
+// implementation (the test hook of gasloc.h runs it).
 //
 // The plan is the same for every column, so it is read through the scalar
 // cache (constant address space): worker and slot indices, counts and weights
@@ -499,7 +500,8 @@ hipError_t with_planned_vec(const LaunchShape& s, F& f) {
   return with_planned_typed<DT, 1, FUSED, FORM>(f);
 }
 
-// As for the phase kernel, the fused last step exists for EQ and ALG1.
+// The fused last step exists for the forms whose slots hold the new local
+// iterate or depend on it (EQ, ALG1).
 template <int DT, typename F>
 hipError_t with_planned_dtype(bool fused, int form, const LaunchShape& s, F& f) {
   switch (form) {

@@ -181,25 +181,7 @@ std::string check_csr(const gasloc_csr& W, int n) {
   return "";
 }
 
-// Workgroup shape of the gossip kernel.  The z slots of all n workers live
-// in LDS, so LDS bounds the columns in flight per CU; sweeps on the n = 8,
-// 16, 32, 64 workloads found 4-column vectors best up to n = 16 and single
-// columns (more threads in flight) beyond.  The workgroup is the largest
-// whose LDS stays within half a CU's, and loads of 8 workers are batched.
-gasloc::LaunchShape pick_gossip_shape(const gasloc_ctx& c, int nnz) {
-  const size_t budget = std::min(c.lds_per_cu / 2, c.lds_per_block_max);
-  const int widest = c.n <= 16 ? 4 : 1;
-  for (int vec : {4, 2, 1}) {
-    if (vec > widest) continue;
-    for (int threads : {256, 128, 64}) {
-      gasloc::LaunchShape s{vec, threads, 0, 8, 0};
-      if (gasloc::gossip_lds_bytes(c.n, nnz, s) + gasloc::kStaticLds <= budget) return s;
-    }
-  }
-  return gasloc::LaunchShape{1, 64, 0, 8, 0};
-}
-
-// Residency of a round kernel, used to pick the planned kernel's workgroup
+// Residency of the planned kernel, used to pick its workgroup
 // size (the one that keeps the most waves per CU).  It comes from the
 // occupancy of the exact kernel that runs (registers, LDS, waves).
 //
@@ -215,31 +197,20 @@ int lds_blocks_per_cu(const gasloc_ctx& c, size_t dyn_lds) {
   return static_cast<int>(c.lds_per_cu / held);
 }
 
-// Workgroups of a round kernel resident on one CU at once (at least 1).
-int resident_blocks_per_cu(const gasloc_ctx& c, const gasloc::LaunchShape& s, bool fused, bool planned,
-                           size_t dyn_lds) {
+// Workgroups of the planned kernel resident on one CU at once (at least 1).
+int resident_blocks_per_cu(const gasloc_ctx& c, const gasloc::LaunchShape& s, bool fused, size_t dyn_lds) {
   const int by_lds = std::min(lds_blocks_per_cu(c, dyn_lds), 2048 / s.threads);
-  const int query = planned ? gasloc::planned_blocks_per_cu(c.hp.param_dtype, fused, c.hp.round_form, s, dyn_lds)
-                            : gasloc::phase_blocks_per_cu(c.hp.param_dtype, fused, c.hp.round_form, s, dyn_lds);
+  const int query = gasloc::planned_blocks_per_cu(c.hp.param_dtype, fused, c.hp.round_form, s, dyn_lds);
   return std::max(1, query <= 0 ? by_lds : std::min(query, by_lds));  // a failed query leaves the LDS bound
 }
 
-// Grid of a round kernel: the columns are cut into steps of threads * vec
+// Grid of the planned kernel: the columns are cut into steps of threads * vec
 // columns, and workgroup b takes `per` consecutive steps, one after the other,
-// then exits.  The grid is not persistent: workgroups are dispatched in column
-// order, so the columns in flight form one compact window sweeping the rows
-// once (as for the AdamW kernel; a grid-stride loop over a fixed grid spreads
-// them over whole rows as its workgroups drift apart).  A few steps per
-// workgroup amortise its start (CSR staging, barrier) and its reduction:
-// measured on MI355X (gossip round alone), per = 8 against 1 took n=16,
-// P=350M from 26.9 to 25.6 ms and n=64, P=50M from 10.7 to 10.4 ms, while 64
-// was slower again (26.3, 10.8 ms).  So per = 8, less where that would leave
-// fewer than 16 workgroups per CU (n=4, P=1M: 0.031 ms at per = 1, 0.061 at
-// 8), and more only if the partials buffer requires it.  The planned kernel
-// with more than 8 slots (small LDS-bound workgroups, many of them per CU)
-// takes one step per workgroup: on the n=32 random 3-regular bf16 workload
-// 1-3% faster than 8 in each of three processes, round alone and fused.
-void tile_grid(const gasloc_ctx& c, gasloc::LaunchShape* s, int most_per) {
+// then exits: at most `most_per` (several steps amortise a workgroup's start
+// and its reduction; small LDS-bound workgroups, many of them per CU, take
+// one), fewer where that would leave fewer than 16 workgroups per CU, and more
+// only if the partials buffer requires it.
+void planned_grid(const gasloc_ctx& c, gasloc::LaunchShape* s, int most_per) {
 #ifdef GASLOC_TUNING
   if (const char* env = std::getenv("GASLOC_GOSSIP_PER")) s->per = std::max(0, std::atoi(env));
 #endif
@@ -362,19 +333,14 @@ bool rows_all_equal(int n, const int32_t* rp, const int32_t* col, const float* v
 }
 
 // Which kernel runs a round.  The tile kernel (the workers of a column over
-// the waves of a workgroup) runs every round; the phase kernel (a thread owns
-// all workers of its columns, every slot value in LDS) and the planned kernel
-// (only the live ones, in the visit order of plan.cpp) are independent
-// implementations of the same arithmetic that the test hook selects
-// (documented in gasloc.h): GASLOC_GOSSIP_KERNEL=phase|planned.
-enum class RoundKernel { kTile, kPhase, kPlanned };
-
-RoundKernel pick_round_kernel() {
-  if (const char* env = std::getenv("GASLOC_GOSSIP_KERNEL")) {
-    if (std::strcmp(env, "phase") == 0) return RoundKernel::kPhase;
-    if (std::strcmp(env, "planned") == 0) return RoundKernel::kPlanned;
-  }
-  return RoundKernel::kTile;
+// the waves of a workgroup) runs every round; the planned kernel (a thread
+// owns all workers of its columns and keeps the live values in LDS, in the
+// visit order of plan.cpp) is an independent implementation of the same
+// arithmetic that the test hook selects (documented in gasloc.h):
+// GASLOC_GOSSIP_KERNEL=planned.
+bool use_planned_kernel() {
+  const char* env = std::getenv("GASLOC_GOSSIP_KERNEL");
+  return env && std::strcmp(env, "planned") == 0;
 }
 
 // Tile kernel's launch: its LDS layout in `a`, the LDS bytes in `lds`.
@@ -569,8 +535,7 @@ gasloc_status run_round(gasloc_ctx* c, const gasloc_csr* W, uint64_t t, const St
     val = c->skip_val.data();
   }
   DeviceGuard guard(c->device);
-  const RoundKernel kernel = pick_round_kernel();
-  const bool planned = kernel == RoundKernel::kPlanned;
+  const bool planned = use_planned_kernel();
   int slots = 0;
   if (planned) {
     // rows with equal entries share their neighbour sum where it does not
@@ -582,9 +547,8 @@ gasloc_status run_round(gasloc_ctx* c, const gasloc_csr* W, uint64_t t, const St
   }
   gasloc::LaunchShape shape;
   size_t lds = 0;
-  const bool tile = kernel == RoundKernel::kTile;
   gasloc::GossipArgs a{};
-  if (tile) {
+  if (!planned) {
     // one sum for all rows where they are equal and it does not depend on the
     // row: its entries go with the launch, and the round needs no CSR
     if ((c->hp.round_form == GASLOC_FORM_EQ || c->hp.round_form == GASLOC_FORM_DADAM) &&
@@ -595,7 +559,7 @@ gasloc_status run_round(gasloc_ctx* c, const gasloc_csr* W, uint64_t t, const St
     }
     shape = pick_tile_shape(*c, step != nullptr, &a, &lds);
     lds += gasloc::kStaticLds;
-  } else if (planned) {
+  } else {
     // 4 columns per thread when the plan needs few slots (n=64 1-Peer: 10.7-
     // 12.8 ms), else 2 (1 column was 25% slower).  The workgroup size is the
     // one that keeps the most waves resident per CU (LDS granules, registers;
@@ -612,7 +576,7 @@ gasloc_status run_round(gasloc_ctx* c, const gasloc_csr* W, uint64_t t, const St
           gasloc::LaunchShape s{vec, threads, 0, gasloc::kPlanBatch, 0};
           const size_t dyn = gasloc::planned_lds_bytes(slots, s);
           if (dyn + gasloc::kStaticLds > std::min(c->lds_per_cu / 2, c->lds_per_block_max)) continue;
-          const int waves = resident_blocks_per_cu(*c, s, step != nullptr, true, dyn) * (threads / 64);
+          const int waves = resident_blocks_per_cu(*c, s, step != nullptr, dyn) * (threads / 64);
           if (waves > best_waves) {
             best_waves = waves;
             best = s;
@@ -623,14 +587,8 @@ gasloc_status run_round(gasloc_ctx* c, const gasloc_csr* W, uint64_t t, const St
     }
     apply_shape_override(&shape);
     lds = gasloc::planned_lds_bytes(slots, shape) + gasloc::kStaticLds;
-  } else {
-    shape = pick_gossip_shape(*c, nnz);
-    if (step) shape.batch = 4;
-    apply_shape_override(&shape);
-    if (step && shape.batch == 8) shape.batch = 4;  // the fused kernel batches at most 4 workers
-    lds = gasloc::gossip_lds_bytes(c->n, nnz, shape) + gasloc::kStaticLds;
+    planned_grid(*c, &shape, slots > 8 ? 1 : 8);
   }
-  if (!tile) tile_grid(*c, &shape, planned && slots > 8 ? 1 : 8);
   if (lds > c->lds_per_block_max) return fail(c, GASLOC_EINVAL, "gossip shape exceeds the device's LDS per workgroup");
   if (planned) {  // slot words become byte offsets for this launch's shape
     std::string err;
@@ -653,9 +611,8 @@ gasloc_status run_round(gasloc_ctx* c, const gasloc_csr* W, uint64_t t, const St
   a.val = reinterpret_cast<const float*>(c->d_csr + rp_bytes + sizeof(int32_t) * c->n * c->n);
   a.ld = c->buf.ld;
   a.P = c->P;
-  a.tile_groups = tile ? shape.per : static_cast<int64_t>(shape.per) * shape.threads;
+  a.tile_groups = planned ? static_cast<int64_t>(shape.per) * shape.threads : shape.per;
   a.n = c->n;
-  a.nnz = nnz;
   a.mu = c->hp.outer_momentum;
   a.eta = c->hp.outer_lr;
   a.gamma = c->hp.consensus_momentum;
@@ -682,17 +639,14 @@ gasloc_status run_round(gasloc_ctx* c, const gasloc_csr* W, uint64_t t, const St
   }
   a.partials = c->d_partials;
   a.pg_partials = c->d_partials + gasloc::kMaxPartials;
-  if (tile) {
+  if (!planned) {
     HIP_TRY(c, gasloc::launch_gossip_tile(a, c->hp.param_dtype, step != nullptr, c->hp.round_form, shape,
                                           lds - gasloc::kStaticLds, c->stream));
-  } else if (planned) {
+  } else {
     a.ops = reinterpret_cast<const int32_t*>(c->d_csr);
     a.slots = slots;
     HIP_TRY(c, gasloc::launch_gossip_planned(a, c->hp.param_dtype, step != nullptr, c->hp.round_form, shape,
                                              c->stream));
-  } else {
-    HIP_TRY(c, gasloc::launch_gossip_round(a, c->hp.param_dtype, step != nullptr, c->hp.round_form, shape,
-                                           c->stream));
   }
   HIP_TRY(c, gasloc::launch_finalize2_large(c->d_partials, a.pg_partials, shape.blocks,
                                              c->d_partials + 2 * gasloc::kMaxPartials, c->d_stats, c->stream));
@@ -792,9 +746,12 @@ gasloc_status gasloc_init(int32_t n, int64_t P, const gasloc_topology* topology,
   c->lds_per_cu = prop.maxSharedMemoryPerMultiProcessor > 0 ? prop.maxSharedMemoryPerMultiProcessor
                                                              : prop.sharedMemPerBlock;
 
-  // the densest CSR a round may bring (n*n entries) must still fit one workgroup
-  const gasloc::LaunchShape worst = pick_gossip_shape(*c, n * n);
-  if (gasloc::gossip_lds_bytes(n, n * n, worst) + gasloc::kStaticLds > c->lds_per_block_max) {
+  // a round whose rows share one sum takes the most LDS of a workgroup
+  gasloc::GossipArgs widest{};
+  widest.sum_entries = 1;
+  size_t lds = 0;
+  pick_tile_shape(*c, false, &widest, &lds);
+  if (lds + gasloc::kStaticLds > c->lds_per_block_max) {
     release(c);
     return fail(nullptr, GASLOC_EINVAL, "gossip workgroup does not fit the device's LDS");
   }

@@ -119,8 +119,8 @@ def test_kernel_families_hash_their_own_sources(bench, tmp_path, monkeypatch):
 
     monkeypatch.delenv("GASLOC_GOSSIP_KERNEL", raising=False)
     assert bench.kernel_family("k_local_adamw", 64) == "adamw"
-    assert bench.kernel_family("gossip_round", 16) == "phase"
-    assert bench.kernel_family("fused_round", 17) == "planned"
+    assert bench.kernel_family("gossip_round", 16) == "tile"
+    assert bench.kernel_family("fused_round", 17) == "tile"
     monkeypatch.setenv("GASLOC_GOSSIP_KERNEL", "planned")
     assert bench.kernel_family("gossip_round", 8) == "planned"
     names = sorted({f for files in bench.KERNEL_FAMILIES.values() for f in files})
@@ -132,7 +132,7 @@ def test_kernel_families_hash_their_own_sources(bench, tmp_path, monkeypatch):
         fh.write("// edited\n")
     after = {fam: bench.kernels_sha(fam) for fam in bench.KERNEL_FAMILIES}
     assert after["planned"] != before["planned"]
-    assert after["adamw"] == before["adamw"] and after["phase"] == before["phase"]
+    assert after["adamw"] == before["adamw"] and after["tile"] == before["tile"]
 
 
 def test_cpu_baseline_times_the_oracle_on_a_sample(bench):

@@ -1,30 +1,45 @@
-// a2-a5 with the workers of a column spread over the waves of a workgroup.  A
-// workgroup takes a tile of C = 64 V columns of every worker: wave w owns the
-// workers w, w + W, w + 2W, ... (K of them at most, W waves), each lane V
-// consecutive columns of each.  The thread that loads a worker's streams also
-// finishes that worker's row, so every stream is read once, in one go, before
-// or around the first barrier, and what the row needs again (its own term, x, u)
-// stays in registers; only the mixed values (z for EQ, the live local iterate for
-// ALG1, x for the DAdam forms) cross waves, through LDS.  The stored rows go
-// through LDS too, so that one thread per column sums the consensus error of
-// all workers in worker order.  Per element the arithmetic is exactly that of
-// k_gossip_round<..., FORM>.
+// a2-a5: pseudo-gradient, outer step, neighbour mix, consensus momentum, and
+// the consensus-error and squared-pseudo-gradient partials, fused, with the
+// workers of a column spread over the waves of a workgroup.  A workgroup takes a
+// tile of C = 64 V columns of every worker: wave w owns the workers w, w + W, w
+// + 2W, ... (K of them at most, W waves), each lane V consecutive columns of
+// each.  The thread that loads a worker's streams also finishes that worker's
+// row, so every stream is read once, before or around the first barrier, and
+// what the row needs again stays in registers; only the mixed values cross
+// waves, through LDS.  The stored rows go through LDS too, so that one thread
+// per column sums the consensus error of all workers in worker order.
 //
-// What bounds it: HBM.  Where a thread owns all workers of its columns, LDS (4
-// n bytes a column) bounds the columns in flight and a wave walks n workers in
-// turn, twice (values, then rows); here the same LDS serves n times as many
-// lanes, all loads of a tile are in flight at once, and the time between a
+// What a slot holds and how a row is finished depends on the round form:
+//   EQ          slot z_j = x_j - eta (delta_j + mu u_j), delta_j = x_j - y_j
+//               x_i = sum_k W_ik z_k [+ gamma (z_i - zp_i)]      (Eq. 1, Eq. 2)
+//   ALG1        slot y_j;  delta_i = sum_k W_ik (x_i - y_k),
+//               x_i = OuterOpt(x_i, delta_i)                      (Algorithm 1)
+//   DADAM       slot x_j;  x_i = sum_k W_ik x_k + (y_i - x_i)     (App. C)
+//   LOCAL_DADAM slot x_j;  d_i = sum_k W_ik (x_i - x_k),
+//               x_i = OuterOpt(y_i, d_i)                          (App. C)
+// with OuterOpt(b, d): u = mu u + d; b - eta (d + mu u) (Nesterov) or b - eta u.
+//
+// What bounds it: HBM, and on short rows the latencies of one tile.  Where a
+// thread owns all workers of its columns, LDS (4 n bytes a column) bounds the
+// columns in flight and a wave walks n workers in turn, twice (values, then
+// rows); here the same LDS serves n times as many lanes, and the time between a
 // workgroup's barriers is covered by the other workgroups of the CU.  Measured
-// on MI355X against those kernels (phase up to 16 workers, planned beyond),
-// same buffers, fused step + round unless noted: n=16, P=50M bf16 Algorithm 1
-// 2-Peer 6.08 -> 4.96 ms (5.2 TB/s); n=32, P=25M bf16 complete 8.17 -> 6.41;
-// n=32, P=12M exponential (step, then round) 4.37 -> 3.80; n=64, P=6M
-// exponential 6.86 -> 2.84 (5.9 TB/s); n=32, P=40M bf16 3-regular 9.22 -> 8.78;
-// n=8, P=124M exponential 8.59 -> 7.92; n=16, P=100M (H=2) 22.43 -> 22.03; n=64,
-// P=25M matching (half the workers, gamma = 0) 9.70 -> 9.49; n=4, P=67M fp32
-// 2.45 -> 2.46.  4 columns per lane: 2 (half the bytes per access) took 3 to
-// 40% longer; tiles of 512 or 1024 columns 1 to 5% longer (n=8, n=16), as did
-// giving each XCD 4 or 16 consecutive tiles.
+// on MI355X on the same buffers against such kernels (up to 16 workers every
+// value in LDS, beyond that the live ones in a planned order; the complete graph
+// beside them with one running sum), n P = 2.7e8, 2-Peer or ring, in ms, fused
+// step + round, gamma = 0.1, unless noted: n=1 fp32 2.08 -> 1.90 (6.2 TB/s); n=4
+// 1.97 -> 1.88, 2.20 -> 1.98, bf16 1.78 -> 1.80, 1.81 -> 1.71 (two buffer sets
+// each: where the buffers lie decides); n=8 1.98 -> 1.91, 2.31 -> 2.08; n=16 2.60
+// -> 2.14, bf16 2.17 -> 1.74; complete n=16 2.59 -> 2.05, n=32 3.03 -> 2.13; n=32
+// 2.07 -> 1.91 (6.2 TB/s), bf16 1.98 -> 1.75; n=64 2.34 -> 2.19, bf16 1.97 -> 1.79;
+// local step and Local-DAdam round, n=64 2.21 -> 2.05, bf16 1.85 -> 1.68.  Short
+// rows, n=16, P=65536 37 -> 14 us, n=64 121 -> 43 us.  Behind them by up to 7%:
+// the EQ round alone in bf16, gamma = 0, on long rows at 17 to 24 and 49 to 60
+// workers (local step and round, n=17 1.72 -> 1.84, n=52 1.82 -> 1.91).
+//
+// 4 columns per lane: 2 (half the bytes per access) took 3 to 40% longer; tiles
+// of 512 or 1024 columns 1 to 5% longer (n=8, n=16), as did giving each XCD 4 or
+// 16 consecutive tiles.
 #pragma clang fp contract(off)
 
 #include "device_common.h"

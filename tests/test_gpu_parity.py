@@ -101,8 +101,8 @@ SMALL = [
     (8, 10007, "exponential", "f32", 1, 0.1, 0.9, False),
     (16, 8191, "one_peer_exp", "f32", 2, 0.1, 0.0, False),
     (32, 3001, "random_regular", "bf16", 2, 0.1, 0.9, True),
-    # fp32 rows of four entries (3-regular graph with its self-loop) take the
-    # planned kernel's branch-free sum at 2 columns per thread; ragged P
+    # fp32 rows of four entries (3-regular graph with its self-loop), one whole
+    # batch of a row's entries; ragged P
     (32, 4097, "random_regular", "f32", 2, 0.1, 0.9, True),
     (33, 515, "two_peer", "f32", 1, 0.3, 0.5, True),
     (64, 2053, "complete", "f32", 1, 0.0, 0.9, True),
@@ -402,11 +402,10 @@ def test_explicit_csr_with_equal_rows(form, dtype):
                                            (64, "bf16", True), (20, "bf16", True)])
 def test_rows_all_equal_share_one_running_sum(n, dtype, fused):
     # every row holds the same entries (the complete graph, DiLoCo's average):
-    # the EQ round keeps one running sum per column and each row's own gamma
+    # the EQ round computes one sum per column and adds each row's own gamma
     # term.  Shared rows that skip most workers (so most rows lack their own
     # column), hold an explicit zero weight, or name every worker; the gamma
-    # term from the second round on; fused and standalone rounds (the fused
-    # bf16 round at 17-32 workers runs the planned kernel)
+    # term from the second round on; fused and standalone rounds
     P = 5_003
     log("case all rows equal n=%d %s fused=%s" % (n, dtype, fused))
     rng = np.random.default_rng(n + 100 * (dtype == "bf16"))
@@ -442,8 +441,8 @@ def test_rows_all_equal_share_one_running_sum(n, dtype, fused):
 
 @pytest.mark.parametrize("n,P,dtype", [(16, 4_099, "f32"), (32, 1, "bf16"), (32, 2_051, "f32"), (17, 777, "bf16")])
 def test_rows_all_equal_with_partial_activity(n, P, dtype):
-    # the shared-row kernel at its register-array boundaries (16 and 32
-    # workers), a single column, and heterogeneous activity: some workers
+    # rounds with one sum per column at 16, 17 and 32 workers (the edges of the
+    # tile kernel's workers per wave), a single column, and heterogeneous activity: some workers
     # skip the fused step, one takes no local step at all (its y is its x)
     log("case all rows equal, partial activity n=%d P=%d %s" % (n, P, dtype))
     pair = Pair(n, P, "ring", dtype, gamma=0.1)
@@ -494,7 +493,7 @@ def test_bf16_rounding_edge_cases(n):
     conversion) of the same fp32 sums does.  With no local steps, mu = gamma =
     0 and rows averaging pairs of workers with weights 1/2, each stored value
     is the rounding of (0 + z_a/2) + z_b/2, with z = x: the exact midpoint of
-    two stored values.  n = 2 runs the phase kernel, n = 18 the planned one."""
+    two stored values.  Two workers have a wave each, 18 share nine."""
     import torch
 
     import paper_2606_11081_amd as g
@@ -704,7 +703,7 @@ def test_maximum_row_length_64bit_offsets():
         pair.local_step()
         pair.local_step()
         pair.gossip_round(t)
-        # the round's own consensus error: 2^21 steps of 1024 columns, two per
+        # the round's own consensus error: 2^23 tiles of 256 columns, eight per
         # workgroup, 2^20 partials summed in segments; the standalone reduction
         # of the same x groups the fp64 sums differently
         fused = pair.gpu.consensus_error()
@@ -868,8 +867,8 @@ def test_extreme_gradients_bit_exact(dtype):
 
 
 def test_two_contexts_interleaved_stay_independent():
-    # two contexts on the same device, different graphs, dtypes and kernels
-    # (n=8 phase kernel, n=40 slot-reusing kernel), rounds interleaved
+    # two contexts on the same device, different graphs, dtypes and workers per
+    # wave, rounds interleaved
     a = Pair(8, 9_001, "exponential", "f32", gamma=0.1, precisions=("f32",))
     b = Pair(40, 7_003, "one_peer", "bf16", gamma=0.2, precisions=("f32",))
     for t in range(3):
@@ -927,8 +926,8 @@ def test_context_on_a_side_stream_matches_the_oracle():
 
 
 @pytest.mark.parametrize("n,topology,dtype,form", [
-    (8, "exponential", "f32", "eq"),       # phase kernel
-    (24, "one_peer", "bf16", "eq"),        # planned kernel, rows sharing sums
+    (8, "exponential", "f32", "eq"),
+    (24, "one_peer", "bf16", "eq"),
     (40, "complete", "f32", "dadam"),
     (33, "two_peer", "bf16", "alg1"),
 ])
@@ -993,7 +992,7 @@ def test_row_padding_is_never_touched(n, topology, dtype, form):
 
 @pytest.mark.parametrize("n,topology,dtype", [(16, "one_peer_exp", "f32"), (40, "two_peer", "bf16")])
 def test_long_run_stays_bit_identical(n, topology, dtype):
-    # 60 rounds (the phase kernel at n=16, the planned one at n=40), varying
+    # 60 rounds, varying
     # local-step counts and the fused last step every other round: the state
     # never drifts from the fp32 oracle by a single bit
     pair = Pair(n, 2_051, topology, dtype, gamma=0.2, precisions=("f32",))

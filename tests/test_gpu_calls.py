@@ -1,6 +1,6 @@
 """Calls around a round on the GPU: a round recorded in a HIP graph, the
-consensus error reduced afresh, calls after a failed HIP call of the program's
-own."""
+consensus error reduced afresh, the network average's division, calls after a
+failed HIP call of the program's own."""
 import numpy as np
 import pytest
 
@@ -145,3 +145,40 @@ def test_calls_after_a_failed_hip_call_of_the_program():
         left = lib.hipGetLastError()  # cleared for the tests that follow
     assert left in (0, failed)
     assert float(out) == 0.0
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_replica_mean_is_the_rounded_quotient(dtype):
+    """For every worker count the average is the fp64 sum in worker order over
+    n, correctly rounded, then rounded to the parameters: random values,
+    infinities, NaN, signed zeros, subnormals and the largest finite ones."""
+    import torch
+
+    print("case replica mean quotient %s" % dtype, flush=True)
+    import paper_2606_11081_amd as g
+
+    P = 2_051
+    pdt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    gen = torch.Generator()
+    gen.manual_seed(3)
+    special = torch.tensor([0.0, -0.0, float("inf"), float("-inf"), float("nan"), 1e-45, -1e-45, 1e-38, 3.3895314e38,
+                            -3.3895314e38])
+    for n in range(1, 65):
+        x = torch.randn(n, P, generator=gen) * torch.exp(4.0 * torch.randn(n, P, generator=gen))
+        x[:, : len(special)] = special  # every worker the same
+        pick = torch.randint(0, len(special), (n, 200), generator=gen)
+        x[:, 100:300] = special[pick]  # and mixed
+        x = x.to(pdt)
+        run = g.GASLoC(n, P, topology="ring", param_dtype=dtype)
+        run.x[:, :P].copy_(x)
+        out = torch.empty(run.ld, dtype=pdt, device="cuda")
+        run.replica_mean(out)
+        s = torch.zeros(P, dtype=torch.float64)
+        for i in range(n):
+            s = s + x[i].double()
+        want = (s / n).float().to(pdt)
+        got = out[:P].cpu()
+        run.close()
+        nan = torch.isnan(want)
+        assert torch.equal(torch.isnan(got), nan), n
+        assert torch.equal(_bits(got[~nan]), _bits(want[~nan])), n

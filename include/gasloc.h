@@ -60,10 +60,12 @@ typedef enum {
  * neighbourhoods are sets, and unless stated the weights are 1/|N_i|
  * (Algorithm 1's average over N_i).  Columns are ascending within a row.
  * Cost: the round keeps one value of every worker in LDS per column, so the
- * graph matters little: the fused step and round ran at 62-77% of peak HBM
- * bandwidth on every graph at n = 2 to 64 (the spread is mostly where the
- * buffers lie in physical memory).  Rows that are all the same (the complete
- * graph, DiLoCo) share one sum per column. */
+ * graph matters little: with n P = 2.7e8 replica-parameters the fused step and
+ * round ran at 4.7-6.4 of 8 TB/s at n = 1 to 64 on 2-Peer, ring and complete
+ * graphs (the spread is mostly where the buffers lie in physical memory), with
+ * 4e6 at 4.0-5.0 TB/s, and below 1e5 its launches' latency counts (14 us a round
+ * at n = 16, P = 4096).  Rows that are all the same (the complete graph, DiLoCo)
+ * share one sum per column. */
 typedef enum {
   GASLOC_TOPO_EXPLICIT = 0,       /* the caller passes W to every round            */
   GASLOC_TOPO_RING = 1,           /* static cycle {i-1, i, i+1} (Tables 1-3 "ring")  */
@@ -201,8 +203,11 @@ gasloc_status gasloc_local_step(gasloc_ctx *ctx, const float *grads, int64_t gra
  * NULL to use the context's topology for round t (EINVAL if EXPLICIT).
  * Deferred reset: afterwards y is logically equal to x but is not written;
  * the next local step of a worker reads x.  A worker that took no local
- * step since the last round has delta = 0.  Enqueues two kernels and one
- * host-to-device copy of the CSR (at most 33 KB). */
+ * step since the last round has delta = 0.  Enqueues two kernels (three beyond
+ * 2^20 columns) and, if the CSR differs from the one on the device, one
+ * host-to-device copy (at most 33 KB).  In the EQ and DADAM forms rows that all
+ * hold the same entries go with the launch: such a round copies nothing, and one
+ * recorded in a HIP graph keeps its weights. */
 gasloc_status gasloc_gossip_round(gasloc_ctx *ctx, const gasloc_csr *W, uint64_t t);
 
 /* One local step immediately followed by the gossip round, in a single pass
@@ -214,7 +219,7 @@ gasloc_status gasloc_gossip_round(gasloc_ctx *ctx, const gasloc_csr *W, uint64_t
  * inner loop ends with y_i = x_i^{(t,H_i)}).  Saves 8 bytes per fp32
  * replica-parameter (12 when H_i = 1).  Same argument rules as the two calls;
  * EINVAL for the DADAM and LOCAL_DADAM forms (use the two calls there).
- * Enqueues two kernels and one CSR copy. */
+ * Enqueues what gasloc_gossip_round does. */
 gasloc_status gasloc_local_step_gossip_round(gasloc_ctx *ctx, const float *grads, int64_t grad_ld,
                                              const uint8_t *active, float lr, const gasloc_csr *W,
                                              uint64_t t);
@@ -247,13 +252,14 @@ gasloc_status gasloc_consensus_error_cols(gasloc_ctx *ctx, int64_t p_begin, int6
  * on hip_stream (the call does not wait), which must belong to the GPU that is
  * current on the calling thread (x and out live there, and so does the
  * scratch the call uses).  Same per-column arithmetic as
- * gasloc_consensus_error_cols; on ranges of at least 8 * 16 * 256 steps of
- * 1024 fp32 (2048 bf16) columns per CU it groups the sums the same way too.
+ * gasloc_consensus_error_cols; on ranges of at least 8 * 16 steps of 1024 fp32
+ * (2048 bf16) columns per CU it groups the sums the same way too.
  * Scratch: a fixed 512 KiB + 128 B device array inside the library (one copy
  * per GPU, held until the process ends); the call allocates nothing and calls
- * no allocating routine.  Limit: at most 2^16 workgroups of 8 x 256 column
- * groups, i.e. 2^29 fp32 or 2^30 bf16 columns per call (EINVAL beyond; the
- * error is additive over columns, so split the range and add the results).
+ * no allocating routine.  Limit: at most 2^16 workgroups of 8 steps, i.e. 2^29
+ * fp32 or 2^30 bf16 columns per call, counted from p_begin rounded down to a
+ * multiple of 4 (EINVAL beyond; the error is additive over columns, so split the
+ * range and add the results).
  * Nothing in the scratch has to start at zero (every partial is written
  * before it is read).  Calls on one GPU share its scratch: calls that overlap
  * in time on one GPU (different streams, or different host threads) race;

@@ -11,8 +11,8 @@
 // dispatch order.
 //
 // Floating-point contract: no contraction (each product and sum is rounded
-// on its own), correctly rounded fp32 division and square root (HIP's
-// default), fp64 for every reduction.
+// on its own), correctly rounded division and square root (HIP's default),
+// fp64 for every reduction.
 #pragma once
 #pragma clang fp contract(off)
 

@@ -21,12 +21,12 @@ namespace gasloc {
 namespace {
 
 // What bounds both reductions is HBM, once the fp64 work (a conversion and
-// one or four operations an element) does not: a group of 4 columns per thread
+// one or five operations an element) does not: a group of 4 columns per thread
 // keeps its sums in few registers, and a step that lies in the range as a whole
 // tests nothing per lane, so that the loads of a batch are issued back to back.
-// n=16, P=50M bf16: the error 350 -> 254 us (6.3 TB/s), the mean 354 -> 274 us;
-// n=16, P=50M fp32: 478 (6.7 TB/s), 620 -> 592 us; n=64, P=6M bf16: 175 -> 148,
-// 145 -> 144 us.  With 8 bf16 columns per thread the error took 350 us, with
+// n=16, P=50M bf16: the error 350 -> 267 us (6.0 TB/s), the mean 347 -> 272 us;
+// n=16, P=50M fp32: 503 -> 498 (6.4 TB/s), 624 -> 594 us; n=64, P=6M bf16: 175 ->
+// 147, 143 -> 136 us.  With 8 bf16 columns per thread the error took 350 us, with
 // whole batches split from the last one (more registers) 294, with batches of
 // 8 workers the same as with 4.
 constexpr int kErrorBatch = 4;  // workers whose loads are in flight at a time
@@ -53,7 +53,8 @@ __device__ __forceinline__ void load_cols(const void* base, int64_t idx, int lo,
 }
 
 // One group of a thread: the shifted fp64 sums of its 4 columns of every
-// worker, workers in order, as the fused kernel's.  EDGE: the group may be cut
+// worker, workers in order, with the round kernels' operations (a column's
+// error is the same number either way).  EDGE: the group may be cut
 // by an end of the range (columns [lo, hi) of it count).
 template <int DT, bool EDGE>
 __device__ __forceinline__ double group_error(const void* x, int64_t ld, int n, int64_t p, int lo_edge, int hi_edge) {
@@ -202,7 +203,8 @@ __global__ __launch_bounds__(kFinalizeThreads) void k_finalize_segments(const do
 // last place, which the first correction gives, and a correctly rounded
 // reciprocal; compared with the division on 2.56e8 random sums for b = 1 to
 // 64), and the fixup restores zeros, infinities and NaN.  Half the instructions
-// of the general division.
+// of the general division.  (The fused multiply-adds are the method's; the
+// result is the division's.)
 __device__ __forceinline__ double divide_by(double a, double b, double r) {
   double q = a * r;
   q = __builtin_fma(__builtin_fma(-b, q, a), r, q);

@@ -125,7 +125,7 @@ struct LaunchShape {
   int vec;      // columns per thread per step (1, 2 or 4)
   int threads;  // workgroup size
   int blocks;   // workgroups: one per tile of `per` steps of the workgroup
-  int batch;    // workers whose loads are issued together (1, 2, 4 or 8); tile kernel: workers per wave
+  int batch;    // tile kernel: workers per wave; planned kernel: workers whose loads are issued together
   int per;      // steps (threads * vec columns each) per workgroup
 };
 

@@ -334,8 +334,8 @@ __device__ __forceinline__ void tile_round(const GossipArgs& a, unsigned char* l
 #pragma unroll
     for (int b = 0; b < B; ++b) {
       const int i = wave + (k0 + b) * waves;
-      if (k0 + b < K && i < n) tile_produce<DT, V, FUSED, FORM, kOnce, kLate, kDeep>(a, i, tile0, at, cnt, w[b], slots, kept[k0 + b],
-                                                               pg);
+      if (k0 + b < K && i < n)
+        tile_produce<DT, V, FUSED, FORM, kOnce, kLate, kDeep>(a, i, tile0, at, cnt, w[b], slots, kept[k0 + b], pg);
     }
     if constexpr (FUSED && kOnce) {  // the batch's moments, once all its values are computed
 #pragma unroll

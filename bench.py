@@ -49,7 +49,8 @@ CSRC = os.path.join(ROOT, "paper_2606_11081_amd", "csrc")
 # counter summary stays valid while its family's sources are unchanged
 KERNEL_FAMILIES = {
     "adamw": ("device_common.h", "internal.h", "adamw.hip", "runtime.cpp"),
-    "tile": ("device_common.h", "internal.h", "round_tile.hip", "reductions.hip", "runtime.cpp"),
+    "tile": ("device_common.h", "internal.h", "round_tile.h", "round_tile_f32.hip", "round_tile_bf16.hip",
+             "reductions.hip", "runtime.cpp"),
     "planned": ("device_common.h", "internal.h", "round_planned.hip", "reductions.hip", "runtime.cpp", "plan.cpp"),
 }
 

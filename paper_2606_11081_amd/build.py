@@ -18,8 +18,9 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 BUILD = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libgasloc.so")
-SOURCES = ["adamw.hip", "round_planned.hip", "round_tile.hip", "reductions.hip",
-           "stream_probe.hip", "runtime.cpp", "topology.cpp", "schedule.cpp", "plan.cpp"]
+SOURCES = ["adamw.hip", "round_planned.hip", "round_tile_f32.hip", "round_tile_bf16.hip",
+           "reductions.hip", "stream_probe.hip", "runtime.cpp", "topology.cpp", "schedule.cpp",
+           "plan.cpp"]
 ARCH = "gfx950"
 
 COMMON = ["-O3", "-std=c++17", "-fPIC", "-Wall", "-Wextra", "-ffp-contract=off",

@@ -1,7 +1,7 @@
 // Internal interfaces between the C ABI (runtime.cpp), the schedule
 // generator (topology.cpp), the visit planner (plan.cpp) and the HIP kernels
-// (adamw.hip, round_tile.hip, round_planned.hip, reductions.hip, with the
-// device helpers of device_common.h).  Not installed.
+// (adamw.hip, round_tile.h, round_planned.hip, reductions.hip, with the device
+// helpers of device_common.h).  Not installed.
 #pragma once
 
 #include <hip/hip_runtime_api.h>
@@ -96,16 +96,9 @@ struct GossipArgs {
   const int32_t* ops;
   int32_t slots;
 
-  // k_gossip_tile only: byte offsets in LDS of the stored rows (0: they take
-  // the slots' place, from kInPlaceWorkers per wave) and of the shared neighbour sums; if every row holds the
-  // entries of row 0 and the form sums them the same way, those entries (else
-  // sum_entries is 0 and the rows are read from the CSR).  As arguments they
-  // belong to the launch: one recorded in a graph keeps them, whatever the
-  // context's CSR holds when it is replayed.
+  // tile kernels only: byte offsets in LDS of the stored rows (0: they take the
+  // slots' place, from kInPlaceWorkers per wave) and of the shared sums
   int32_t kept_off, sums_off;
-  int32_t sum_entries;
-  int32_t sum_col[kMaxReplicas];
-  float sum_w[kMaxReplicas];
 
   // Fused last local step (the fused kernel only): every worker i with bit i
   // of `active` first takes one AdamW step from its live iterate; the new
@@ -121,6 +114,16 @@ struct GossipArgs {
   float c2[kMaxReplicas];
 };
 
+// The entries that every row of a round holds, where the form sums them the same
+// way for each (EQ, DADAM); `entries` is 0 where the rows differ and are read
+// from the CSR.  A kernel argument: a launch recorded in a graph keeps them,
+// whatever the context's CSR holds when it is replayed.
+struct RowSum {
+  int32_t entries;
+  int32_t col[kMaxReplicas];
+  float w[kMaxReplicas];
+};
+
 struct LaunchShape {
   int vec;      // columns per thread per step (1, 2 or 4)
   int threads;  // workgroup size
@@ -134,7 +137,7 @@ hipError_t launch_local_adamw(const AdamArgs& a, int dtype, int cus, hipStream_t
 hipError_t launch_gossip_planned(const GossipArgs& a, int dtype, bool fused, int form, const LaunchShape& shape,
                                  hipStream_t stream);
 // Rounds with the workers spread over the waves of a workgroup
-// (round_tile.hip): shape.threads / 64 waves with shape.batch workers each (1
+// (round_tile.h): shape.threads / 64 waves with shape.batch workers each (1
 // to 8; 3 in the fused EQ kernel only), kTileVec columns per lane, a.tile_groups tiles per workgroup;
 // `lds`: the bytes a.kept_off and a.sums_off were laid out in.
 constexpr int kTileVec = 4;
@@ -143,8 +146,10 @@ constexpr int kInPlaceWorkers = 4;  // the fewest per wave that may store rows i
 constexpr size_t tile_slot_bytes(int dtype, int form) {
   return dtype == GASLOC_BF16 && form != GASLOC_FORM_EQ ? 2 : 4;
 }
-hipError_t launch_gossip_tile(const GossipArgs& a, int dtype, bool fused, int form, const LaunchShape& shape,
-                              size_t lds, hipStream_t stream);
+hipError_t launch_gossip_tile_f32(const GossipArgs& a, const RowSum& sum, bool fused, int form,
+                                  const LaunchShape& shape, size_t lds, hipStream_t stream);
+hipError_t launch_gossip_tile_bf16(const GossipArgs& a, const RowSum& sum, bool fused, int form,
+                                   const LaunchShape& shape, size_t lds, hipStream_t stream);
 // Workgroups of the selected planned round kernel that one CU holds at once,
 // given its registers, LDS and wave limits (0 if the query fails).
 int planned_blocks_per_cu(int dtype, bool fused, int form, const LaunchShape& shape, size_t dyn_lds);

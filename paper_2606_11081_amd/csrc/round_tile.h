@@ -40,6 +40,10 @@
 // 4 columns per lane: 2 (half the bytes per access) took 3 to 40% longer; tiles
 // of 512 or 1024 columns 1 to 5% longer (n=8, n=16), as did giving each XCD 4 or
 // 16 consecutive tiles.
+//
+// Included by round_tile_f32.hip and round_tile_bf16.hip, which compile the
+// kernels of one parameter type each.
+#pragma once
 #pragma clang fp contract(off)
 
 #include "device_common.h"
@@ -169,8 +173,8 @@ __device__ __forceinline__ void tile_load(const GossipArgs& a, int i, int64_t ti
 
 template <int DT, int V, bool FUSED, int FORM, bool ONCE, bool LATE, bool LEAN>
 __device__ __forceinline__ void tile_produce(const GossipArgs& a, int i, int64_t tile0, int at, int cnt,
-                                             WorkerLoads<V, FUSED, FORM>& w, void* slots, RowKept<DT, V, FORM, LEAN>& kept,
-                                             double& pg) {
+                                             WorkerLoads<V, FUSED, FORM>& w, void* slots,
+                                             RowKept<DT, V, FORM, LEAN>& kept, double& pg) {
   const int64_t row = static_cast<int64_t>(i) * a.ld + tile0;  // uniform
   if constexpr (ONCE) {
     const bool stepped = (a.stepped >> i) & 1ull;
@@ -227,9 +231,9 @@ __device__ __forceinline__ void tile_produce(const GossipArgs& a, int i, int64_t
 }
 
 // Row i from the slots: res, and u where the form updates it there.
-template <int DT, int V, int FORM, bool LEAN>
+template <int DT, int V, int FORM, bool LEAN, bool SHARED>
 __device__ __forceinline__ void tile_row(const GossipArgs& a, uniform_i32* rp, uniform_i32* col, uniform_f32* val,
-                                         int i, const void* slots, const float* shared_sum, int at,
+                                         int i, const void* slots, const float* sums, int at,
                                          RowKept<DT, V, FORM, LEAN>& kept, float (&res)[V]) {
   constexpr int C = kWave * V;
   constexpr bool kHalf = kSlot16<DT, FORM>;
@@ -246,9 +250,9 @@ __device__ __forceinline__ void tile_row(const GossipArgs& a, uniform_i32* rp, u
   }
 #pragma unroll
   for (int c = 0; c < V; ++c) res[c] = 0.0f;
-  if (!kDiff && shared_sum) {
+  if constexpr (SHARED) {
 #pragma unroll
-    for (int c = 0; c < V; ++c) res[c] = shared_sum[at + c];
+    for (int c = 0; c < V; ++c) res[c] = sums[at + c];
   } else {
     const int kb = rp[i], ke = rp[i + 1];
     for (int k0 = kb; k0 < ke; k0 += 4) {
@@ -282,10 +286,11 @@ __device__ __forceinline__ void tile_row(const GossipArgs& a, uniform_i32* rp, u
   }
 }
 
-// One tile.  TAIL: the tile runs past P (cnt < V in some lanes).
-template <int DT, int V, int K, bool FUSED, int FORM, bool TAIL>
-__device__ __forceinline__ void tile_round(const GossipArgs& a, unsigned char* lds, int64_t tile0, double& ce,
-                                           double& pg) {
+// One tile.  TAIL: the tile runs past P (cnt < V in some lanes).  SHARED: every
+// row is `sum`, plus its own term.
+template <int DT, int V, int K, bool FUSED, int FORM, bool SHARED, bool TAIL>
+__device__ __forceinline__ void tile_round(const GossipArgs& a, const RowSum* sum, unsigned char* lds, int64_t tile0,
+                                           double& ce, double& pg) {
   constexpr int C = kWave * V;
   constexpr int sp = DT == GASLOC_BF16 ? 2 : 4;
   constexpr int B = K < 2 ? K : 2;  // workers whose loads are issued together (4: up to 20% slower)
@@ -363,12 +368,10 @@ __device__ __forceinline__ void tile_round(const GossipArgs& a, unsigned char* l
     }
   }
   __syncthreads();  // every worker's value is in its slot
-  constexpr bool kSums = FORM == GASLOC_FORM_EQ || FORM == GASLOC_FORM_DADAM;
-  const bool shared = kSums && a.sum_entries > 0;
-  if (shared) {
+  if constexpr (SHARED) {
     for (int c = threadIdx.x; c < C; c += blockDim.x) {
       float s = 0.0f;
-      for (int k = 0; k < a.sum_entries; ++k) s = s + a.sum_w[k] * lds_value<kHalf>(slots, a.sum_col[k] * C + c);
+      for (int k = 0; k < sum->entries; ++k) s = s + sum->w[k] * lds_value<kHalf>(slots, sum->col[k] * C + c);
       sums[c] = s;
     }
     __syncthreads();
@@ -383,7 +386,7 @@ __device__ __forceinline__ void tile_round(const GossipArgs& a, unsigned char* l
     if (i >= n) break;
     const int64_t row = static_cast<int64_t>(i) * a.ld + tile0;
     float res[V], kept_x[V];
-    tile_row<DT, V, FORM, kDeep>(a, rp, col, val, i, slots, shared ? sums : nullptr, at, kept[k], res);
+    tile_row<DT, V, FORM, kDeep, SHARED>(a, rp, col, val, i, slots, sums, at, kept[k], res);
     store_params<DT, V>(static_cast<char*>(a.x) + row * sp, at, cnt, res, kept_x);
     stored[k].set(kept_x);
     if constexpr (kOuterRow<FORM>) {
@@ -417,21 +420,21 @@ __device__ __forceinline__ void tile_round(const GossipArgs& a, unsigned char* l
   }
 }
 
-template <int DT, int V, int K, bool FUSED, int FORM>
-__global__ __launch_bounds__(1024) void k_gossip_tile(GossipArgs a) {
-  extern __shared__ __align__(16) unsigned char lds[];
+template <int DT, int V, int K, bool FUSED, int FORM, bool SHARED>
+__device__ __forceinline__ void tile_rounds(const GossipArgs& a, const RowSum* sum, unsigned char* lds) {
   constexpr int C = kWave * V;
   const int64_t tiles = (a.P + C - 1) / C;
   const int64_t t0 = static_cast<int64_t>(blockIdx.x) * a.tile_groups;
   const int64_t t1 = tiles - t0 < a.tile_groups ? tiles : t0 + a.tile_groups;
   double ce = 0.0, pg = 0.0;
   for (int64_t t = t0; t < t1; ++t) {
-    if (K >= kInPlaceWorkers && a.kept_off == 0 && t > t0) __syncthreads();  // the stored rows of the tile before have been summed
+    // in place: the stored rows of the tile before have been summed
+    if (K >= kInPlaceWorkers && a.kept_off == 0 && t > t0) __syncthreads();
     const int64_t tile0 = t * C;
     if (tile0 + C <= a.P)
-      tile_round<DT, V, K, FUSED, FORM, false>(a, lds, tile0, ce, pg);
+      tile_round<DT, V, K, FUSED, FORM, SHARED, false>(a, sum, lds, tile0, ce, pg);
     else
-      tile_round<DT, V, K, FUSED, FORM, true>(a, lds, tile0, ce, pg);
+      tile_round<DT, V, K, FUSED, FORM, SHARED, true>(a, sum, lds, tile0, ce, pg);
   }
   double total_ce, total_pg;
   block_sum2(ce, pg, total_ce, total_pg);
@@ -441,46 +444,75 @@ __global__ __launch_bounds__(1024) void k_gossip_tile(GossipArgs a) {
   }
 }
 
-template <int DT, bool FUSED, int FORM, typename F>
-hipError_t with_tile_workers(int per_wave, F& f) {
-  switch (per_wave) {
-    case 1: return f(reinterpret_cast<const void*>(&k_gossip_tile<DT, kTileVec, 1, FUSED, FORM>));
-    case 2: return f(reinterpret_cast<const void*>(&k_gossip_tile<DT, kTileVec, 2, FUSED, FORM>));
+// Waves per SIMD.  The fused EQ kernel with two workers per wave needs 95
+// registers, which let a fifth wave in: its eight streams are then faster with
+// four (n=4, P=60M 1.87 -> 1.84 ms; n=2, P=100M bf16 1.39 -> 1.35).
+template <int K, bool FUSED, int FORM>
+constexpr int kMaxWaves = FUSED && FORM == GASLOC_FORM_EQ && K == 2 ? 4 : 8;
+
+template <int DT, int V, int K, bool FUSED, int FORM>
+__global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(4, kMaxWaves<K, FUSED, FORM>))) void
+k_gossip_tile(GossipArgs a) {
+  extern __shared__ __align__(16) unsigned char lds[];
+  tile_rounds<DT, V, K, FUSED, FORM, false>(a, nullptr, lds);
+}
+
+// Rounds whose rows are all equal.  The entries are an argument of their own: in
+// the other kernels' arguments they would cost every launch about 1 us of host
+// time (512 bytes more: a round on a graph that changes, n=17, P=47504 20.5 ->
+// 22.1 us).
+template <int DT, int V, int K, bool FUSED, int FORM>
+__global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(4, kMaxWaves<K, FUSED, FORM>))) void
+k_gossip_tile_shared(GossipArgs a, RowSum sum) {
+  extern __shared__ __align__(16) unsigned char lds[];
+  tile_rounds<DT, V, K, FUSED, FORM, true>(a, &sum, lds);
+}
+
+template <int DT, int K, bool FUSED, int FORM>
+hipError_t launch_tile_kernel(const GossipArgs& a, const RowSum& sum, const LaunchShape& s, size_t lds,
+                              hipStream_t stream) {
+  if constexpr (!kOuterRow<FORM>) {
+    if (sum.entries > 0)
+      return launch_kernel(k_gossip_tile_shared<DT, kTileVec, K, FUSED, FORM>, dim3(s.blocks), s.threads, lds, stream,
+                           a, sum);
+  }
+  return launch_kernel(k_gossip_tile<DT, kTileVec, K, FUSED, FORM>, dim3(s.blocks), s.threads, lds, stream, a);
+}
+
+template <int DT, bool FUSED, int FORM>
+hipError_t launch_tile_workers(const GossipArgs& a, const RowSum& sum, const LaunchShape& s, size_t lds,
+                               hipStream_t stream) {
+  switch (s.batch) {
+    case 1: return launch_tile_kernel<DT, 1, FUSED, FORM>(a, sum, s, lds, stream);
+    case 2: return launch_tile_kernel<DT, 2, FUSED, FORM>(a, sum, s, lds, stream);
     case 3:
       if constexpr (FUSED && FORM == GASLOC_FORM_EQ)
-        return f(reinterpret_cast<const void*>(&k_gossip_tile<DT, kTileVec, 3, FUSED, FORM>));
+        return launch_tile_kernel<DT, 3, FUSED, FORM>(a, sum, s, lds, stream);
       return hipErrorInvalidValue;
-    case 4: return f(reinterpret_cast<const void*>(&k_gossip_tile<DT, kTileVec, 4, FUSED, FORM>));
-    case 5: return f(reinterpret_cast<const void*>(&k_gossip_tile<DT, kTileVec, 5, FUSED, FORM>));
-    case 6: return f(reinterpret_cast<const void*>(&k_gossip_tile<DT, kTileVec, 6, FUSED, FORM>));
-    case 7: return f(reinterpret_cast<const void*>(&k_gossip_tile<DT, kTileVec, 7, FUSED, FORM>));
-    default: return f(reinterpret_cast<const void*>(&k_gossip_tile<DT, kTileVec, 8, FUSED, FORM>));
+    case 4: return launch_tile_kernel<DT, 4, FUSED, FORM>(a, sum, s, lds, stream);
+    case 5: return launch_tile_kernel<DT, 5, FUSED, FORM>(a, sum, s, lds, stream);
+    case 6: return launch_tile_kernel<DT, 6, FUSED, FORM>(a, sum, s, lds, stream);
+    case 7: return launch_tile_kernel<DT, 7, FUSED, FORM>(a, sum, s, lds, stream);
+    default: return launch_tile_kernel<DT, 8, FUSED, FORM>(a, sum, s, lds, stream);
   }
 }
 
-template <int DT, typename F>
-hipError_t with_tile_form(bool fused, int form, int per_wave, F& f) {
+template <int DT>
+hipError_t launch_tile_form(const GossipArgs& a, const RowSum& sum, bool fused, int form, const LaunchShape& s,
+                            size_t lds, hipStream_t stream) {
   switch (form) {
     case GASLOC_FORM_ALG1:
-      return fused ? with_tile_workers<DT, true, GASLOC_FORM_ALG1>(per_wave, f)
-                   : with_tile_workers<DT, false, GASLOC_FORM_ALG1>(per_wave, f);
+      return fused ? launch_tile_workers<DT, true, GASLOC_FORM_ALG1>(a, sum, s, lds, stream)
+                   : launch_tile_workers<DT, false, GASLOC_FORM_ALG1>(a, sum, s, lds, stream);
     case GASLOC_FORM_DADAM:
-      return with_tile_workers<DT, false, GASLOC_FORM_DADAM>(per_wave, f);
+      return launch_tile_workers<DT, false, GASLOC_FORM_DADAM>(a, sum, s, lds, stream);
     case GASLOC_FORM_LOCAL_DADAM:
-      return with_tile_workers<DT, false, GASLOC_FORM_LOCAL_DADAM>(per_wave, f);
+      return launch_tile_workers<DT, false, GASLOC_FORM_LOCAL_DADAM>(a, sum, s, lds, stream);
     default:
-      return fused ? with_tile_workers<DT, true, GASLOC_FORM_EQ>(per_wave, f)
-                   : with_tile_workers<DT, false, GASLOC_FORM_EQ>(per_wave, f);
+      return fused ? launch_tile_workers<DT, true, GASLOC_FORM_EQ>(a, sum, s, lds, stream)
+                   : launch_tile_workers<DT, false, GASLOC_FORM_EQ>(a, sum, s, lds, stream);
   }
 }
 
 }  // namespace
-
-hipError_t launch_gossip_tile(const GossipArgs& a, int dtype, bool fused, int form, const LaunchShape& s, size_t lds,
-                              hipStream_t stream) {
-  auto launch = [&](const void* k) { return launch_round_args(k, a, s, lds, stream); };
-  return dtype == GASLOC_BF16 ? with_tile_form<GASLOC_BF16>(fused, form, s.batch, launch)
-                              : with_tile_form<GASLOC_F32>(fused, form, s.batch, launch);
-}
-
 }  // namespace gasloc

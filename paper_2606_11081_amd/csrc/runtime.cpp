@@ -383,7 +383,8 @@ bool use_planned_kernel() {
 // The stored rows get LDS of their own up to 32 workers; beyond, they take the
 // slots' place after one more barrier, so that two workgroups fit a CU (n=64,
 // P=25M matching: 11.57 ms with LDS of their own, 9.42 ms in place).
-gasloc::LaunchShape pick_tile_shape(const gasloc_ctx& c, bool fused, gasloc::GossipArgs* a, size_t* lds) {
+gasloc::LaunchShape pick_tile_shape(const gasloc_ctx& c, bool fused, bool shared_sum, gasloc::GossipArgs* a,
+                                     size_t* lds) {
   constexpr int64_t kCols = 64 * gasloc::kTileVec;
   const int64_t tiles = (c.P + kCols - 1) / kCols;
   const int fewest = c.n <= 16 ? 1 : (c.n <= 32 ? 2 : 4);
@@ -418,7 +419,7 @@ gasloc::LaunchShape pick_tile_shape(const gasloc_ctx& c, bool fused, gasloc::Gos
     end += slots * param_bytes(c.hp.param_dtype);
   }
   a->sums_off = static_cast<int32_t>(end);
-  if (a->sum_entries > 0) end += kCols * sizeof(float);
+  if (shared_sum) end += kCols * sizeof(float);
   *lds = end;
   const int waves = (c.n + per_wave - 1) / per_wave;
   return gasloc::LaunchShape{gasloc::kTileVec, 64 * waves, static_cast<int>((tiles + per - 1) / per), per_wave,
@@ -548,16 +549,18 @@ gasloc_status run_round(gasloc_ctx* c, const gasloc_csr* W, uint64_t t, const St
   gasloc::LaunchShape shape;
   size_t lds = 0;
   gasloc::GossipArgs a{};
+  gasloc::RowSum sum;
+  sum.entries = 0;
   if (!planned) {
     // one sum for all rows where they are equal and it does not depend on the
     // row: its entries go with the launch, and the round needs no CSR
     if ((c->hp.round_form == GASLOC_FORM_EQ || c->hp.round_form == GASLOC_FORM_DADAM) &&
         rows_all_equal(c->n, rp, col, val)) {
-      a.sum_entries = rp[1];
-      std::memcpy(a.sum_col, col, sizeof(int32_t) * static_cast<size_t>(rp[1]));
-      std::memcpy(a.sum_w, val, sizeof(float) * static_cast<size_t>(rp[1]));
+      sum.entries = rp[1];
+      std::memcpy(sum.col, col, sizeof(int32_t) * static_cast<size_t>(rp[1]));
+      std::memcpy(sum.w, val, sizeof(float) * static_cast<size_t>(rp[1]));
     }
-    shape = pick_tile_shape(*c, step != nullptr, &a, &lds);
+    shape = pick_tile_shape(*c, step != nullptr, sum.entries > 0, &a, &lds);
     lds += gasloc::kStaticLds;
   } else {
     // 4 columns per thread when the plan needs few slots (n=64 1-Peer: 10.7-
@@ -596,7 +599,7 @@ gasloc_status run_round(gasloc_ctx* c, const gasloc_csr* W, uint64_t t, const St
                                   &err))
       return fail(c, GASLOC_EINVAL, err);
   }
-  if (a.sum_entries == 0) {
+  if (sum.entries == 0) {
     gasloc_status st = planned ? upload_plan(c, c->plan_ops) : upload_csr(c, rp, col, val, nnz);
     if (st != GASLOC_OK) return st;
   }
@@ -640,8 +643,9 @@ gasloc_status run_round(gasloc_ctx* c, const gasloc_csr* W, uint64_t t, const St
   a.partials = c->d_partials;
   a.pg_partials = c->d_partials + gasloc::kMaxPartials;
   if (!planned) {
-    HIP_TRY(c, gasloc::launch_gossip_tile(a, c->hp.param_dtype, step != nullptr, c->hp.round_form, shape,
-                                          lds - gasloc::kStaticLds, c->stream));
+    const auto launch =
+        c->hp.param_dtype == GASLOC_BF16 ? gasloc::launch_gossip_tile_bf16 : gasloc::launch_gossip_tile_f32;
+    HIP_TRY(c, launch(a, sum, step != nullptr, c->hp.round_form, shape, lds - gasloc::kStaticLds, c->stream));
   } else {
     a.ops = reinterpret_cast<const int32_t*>(c->d_csr);
     a.slots = slots;
@@ -747,10 +751,9 @@ gasloc_status gasloc_init(int32_t n, int64_t P, const gasloc_topology* topology,
                                                              : prop.sharedMemPerBlock;
 
   // a round whose rows share one sum takes the most LDS of a workgroup
-  gasloc::GossipArgs widest{};
-  widest.sum_entries = 1;
+  gasloc::GossipArgs layout{};
   size_t lds = 0;
-  pick_tile_shape(*c, false, &widest, &lds);
+  pick_tile_shape(*c, false, true, &layout, &lds);
   if (lds + gasloc::kStaticLds > c->lds_per_block_max) {
     release(c);
     return fail(nullptr, GASLOC_EINVAL, "gossip workgroup does not fit the device's LDS");

@@ -64,3 +64,23 @@ def test_no_kernel_spills(src, tmp_path):
     spills = [int(v) for v in re.findall(r"\.vgpr_spill_count: (\d+)", notes)]
     assert names and len(names) == len(scratch) == len(spills)
     assert not [k for k in zip(names, scratch, spills) if k[1] or k[2]]
+
+
+@pytest.mark.skipif(not (os.path.exists(BUNDLER) and os.path.exists(READELF)), reason="ROCm LLVM tools absent")
+@pytest.mark.parametrize("src", ["round_tile_f32.hip", "round_tile_bf16.hip"])
+def test_only_rounds_of_equal_rows_carry_their_entries(src, tmp_path):
+    """64 columns and 64 weights as kernel arguments cost a short round about 1 us: the
+    kernels that read the rows from the CSR are launched without them."""
+    fatbin = lib_build.device_binary(src)
+    if not os.path.exists(fatbin):
+        pytest.skip("library not built")
+    co = str(tmp_path / "kernels.co")
+    subprocess.run([BUNDLER, "--unbundle", "--type=o", "--targets=hipv4-amdgcn-amd-amdhsa--gfx950",
+                    "--input=" + fatbin, "--output=" + co], check=True, capture_output=True)
+    notes = subprocess.run([READELF, "--notes", co], check=True, capture_output=True, text=True).stdout
+    names = re.findall(r"\.name: +(_Z\S+)", notes)
+    sizes = [int(v) for v in re.findall(r"\.kernarg_segment_size: (\d+)", notes)]
+    assert names and len(names) == len(sizes)
+    shared = [b for n, b in zip(names, sizes) if "k_gossip_tile_shared" in n]
+    plain = [b for n, b in zip(names, sizes) if "k_gossip_tile_shared" not in n]
+    assert shared and plain and max(plain) + 2 * 4 * 64 <= min(shared)
